@@ -263,102 +263,198 @@ void wgrad_chunks(int64_t n_out, int tiles, int64_t* chunks, int64_t* V) {
 
 // ---- linear layers backward (the classifier fused with DeformSlice, the
 // 1x1 layers of Distribute + PointNet) ----
-// For out_p = W a_p + b over rows p (W: K x C, [out][in]) and G = dL/dout:
-//   dA_p = sum_j G_pj W[j]   (k_lin_dinput),
-//   dW = sum_p G_p a_p^T, db = sum_p G_p   (k_lin_wgrad over chunks of rows,
-//   then k_lin_reduce adds the chunks' partials in chunk order).
-// a_p is either given or max(x_p scale + shift, 0) of given rows x_p (the
-// pre-activation table pre = [C scales][C shifts]).
-constexpr int kClsPts = 32;        // rows staged per step of k_lin_wgrad
-constexpr int kClsMaxChunks = 1024;
+// For out_p = W a_p + b over m rows p (W: K x C, [out][in]) and z = dL/dout:
+//   dA_p = sum_j z_pj W[j]   (k_lin_dinput),
+//   dW = sum_p z_p a_p^T, db = sum_p z_p   (k_lin_wgrad over chunks of rows,
+//   then k_lin_reduce adds the chunks' partials).
+// Both products run on v_mfma_f32_16x16x4_f32 with operands loaded straight
+// into its layout (16 bytes a lane), 64 columns of C per workgroup: rows are
+// read once per column block and nothing but the weights is staged, so the
+// passes are bound by the rows' memory traffic.  At 480,000 rows, K = 64, C =
+// 32 (the last PointNet layer of a LiDAR scan) they took 192 (dA), 279 (dW)
+// and 239 us (the partials, one thread per output over 1,000 of them) as FMA
+// loops, and 62, 76 and 6 us here; at 200,000 rows, K = 20, C = 128 (the head of
+// a room) 91, 147 and 215 us, and 38, 38 and 6 us here.
+constexpr int kLinCols = 64;        // columns of C per workgroup
+constexpr int kLinMaxChunks = 1024;
+constexpr int64_t kLinMaxPartial = 4 << 20;   // floats of partials aimed at
+constexpr int kLinRedOut = 16, kLinRedSlices = kBlock / kLinRedOut;
 
-// dA_p[c] = sum_j G_pj W[j][c]: one thread per (row, 4 channels).
+// dA (m x C): 16 rows a step and wave.  A = W^T (LDS, fragment order), B = z^T:
+// lane (i, g) holds z[p0 + i][16 jb + 4 g + s] for step s of block jb, and
+// receives dA[p0 + i][c0 + 16 nb + 4 g + r].  V4: rows of z allow 16-byte loads.
+template <int KB, bool V4>
 __global__ void __launch_bounds__(kBlock)
-k_lin_dinput(const float* __restrict__ z, int64_t ld_z, const float* __restrict__ Wc, int K, int C, int64_t m,
+k_lin_dinput(const float* __restrict__ z, int64_t ld_z, const float* __restrict__ W, int K, int C, int64_t m,
              float* __restrict__ df, int64_t ld_df) {
-  const int quads = C / 4;
-  const int64_t total = m * quads;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < total;
-       i += static_cast<int64_t>(gridDim.x) * kBlock) {
-    const int64_t p = i / quads;
-    const int c = 4 * static_cast<int>(i - p * quads);
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j = 0; j < K; ++j) {
-      const float zj = z[p * ld_z + j];
-      const float4 w = *reinterpret_cast<const float4*>(Wc + static_cast<int64_t>(j) * C + c);
-      a.x = fmaf(zj, w.x, a.x);
-      a.y = fmaf(zj, w.y, a.y);
-      a.z = fmaf(zj, w.z, a.z);
-      a.w = fmaf(zj, w.w, a.w);
+  __shared__ __align__(16) float ws[KB * 4 * 64 * 4];   // [jb][nb][lane][s]
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  const int c0 = blockIdx.y * kLinCols;
+  for (int q = t; q < KB * 4 * 64 * 4; q += kBlock) {
+    const int s = q & 3, L = (q >> 2) & 63, nb = (q >> 8) & 3, jb = q >> 10;
+    const int j = 16 * jb + 4 * (L >> 4) + s, c = c0 + 16 * nb + (L & 15);
+    ws[q] = (j < K && c < C) ? W[static_cast<int64_t>(j) * C + c] : 0.f;
+  }
+  __syncthreads();
+  const int64_t groups = (m + 15) / 16;
+  const f32x4* wf = reinterpret_cast<const f32x4*>(ws) + lane;
+  const int64_t step = static_cast<int64_t>(gridDim.x) * 4;
+  auto load = [&](int64_t grp, float (&zr)[KB][4]) {
+    const int64_t p = grp * 16 + li;
+#pragma unroll
+    for (int jb = 0; jb < KB; ++jb) {
+      const int j = 16 * jb + 4 * lg;
+      if constexpr (V4) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (p < m && j < K) v = *reinterpret_cast<const float4*>(z + p * ld_z + j);
+        zr[jb][0] = v.x; zr[jb][1] = v.y; zr[jb][2] = v.z; zr[jb][3] = v.w;
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) zr[jb][s] = (p < m && j + s < K) ? z[p * ld_z + j + s] : 0.f;
+      }
     }
-    *reinterpret_cast<float4*>(df + p * ld_df + c) = a;
+  };
+  float zc[KB][4], zn[KB][4];
+  int64_t grp = static_cast<int64_t>(blockIdx.x) * 4 + wave;
+  if (grp < groups) load(grp, zc);
+  for (; grp < groups; grp += step) {
+    load(grp + step, zn);   // past the last row: zeros, no access
+    f32x4 acc[4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int jb = 0; jb < KB; ++jb) {
+      f32x4 w[4];
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) w[nb] = wf[(jb * 4 + nb) * 64];
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+          acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][s], zc[jb][s], acc[nb], 0, 0, 0);
+    }
+    const int64_t p = grp * 16 + li;
+    if (p < m) {
+      float* o = df + p * ld_df + c0 + 4 * lg;
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb)
+        if (c0 + 16 * nb + 4 * lg < C) *reinterpret_cast<f32x4*>(o + 16 * nb) = acc[nb];
+    }
+#pragma unroll
+    for (int jb = 0; jb < KB; ++jb)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) zc[jb][s] = zn[jb][s];
   }
 }
 
-// Workgroup w: over its chunk of rows, part[w][j C + c] = sum_p G_pj a_pc and
-// part[w][K C + j] = sum_p G_pj, rows in order; rows of G and a are staged
-// kClsPts at a time in LDS (a pre-activated as they are staged when pre is
-// given).  Thread t owns outputs t, t + 256, ...
-template <int NO>
+// Workgroup (w, cb): over chunk w of the rows, part[w][j C + c] = sum_p z_pj
+// a_pc for the columns of block cb, and for cb = 0 part[w][K C + j] = sum_p
+// z_pj.  A = z^T: lane (i, g) holds z[p + g][16 jb + i]; B = a: the lane's
+// float4 a[p + g][c0 + 4 i ..] feeds four products whose column i stands for
+// c0 + 4 i + nb.  The four waves take 16 rows each in turn and are added in
+// wave order.
+template <int KB>
 __global__ void __launch_bounds__(kBlock)
-k_lin_wgrad(const float* __restrict__ z, int64_t ld_z, const float* __restrict__ f, int64_t ld_f,
-            const float* __restrict__ pre, int K, int C, int64_t m, int64_t chunk, float* __restrict__ part) {
-  extern __shared__ float sm[];
-  float* sz = sm;                    // [kClsPts][K]
-  float* sf = sm + kClsPts * K;      // [kClsPts][C]
-  const int t = threadIdx.x;
-  const int nout = K * C + K;
+k_lin_wgrad(const float* __restrict__ z, int64_t ld_z, const float* __restrict__ f, int64_t ld_f, int K, int C,
+            int64_t m, int64_t chunk, float* __restrict__ part) {
+  __shared__ float sum[KB * 16 * kLinCols];   // [j][c]
+  __shared__ float sb[4][KB * 16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  const int c0 = blockIdx.y * kLinCols;
   const int64_t p0 = static_cast<int64_t>(blockIdx.x) * chunk;
   const int64_t p1 = min(p0 + chunk, m);
-  float acc[NO];
+  const bool col_ok = c0 + 4 * li < C;
+  constexpr int S = KB > 2 ? 4 : 8;   // rows in flight per lane
+  f32x4 acc[KB][4];
+  float bs[KB];
 #pragma unroll
-  for (int k = 0; k < NO; ++k) acc[k] = 0.f;
-  for (int64_t pb = p0; pb < p1; pb += kClsPts) {
-    const int np = static_cast<int>(min<int64_t>(kClsPts, p1 - pb));
-    __syncthreads();
-    for (int e = t; e < np * K; e += kBlock) sz[e] = z[(pb + e / K) * ld_z + e % K];
-    for (int e = t; e < np * (C / 4); e += kBlock) {
-      const int r = e / (C / 4), q = e - r * (C / 4);
-      float4 v = *reinterpret_cast<const float4*>(f + (pb + r) * ld_f + 4 * q);
-      if (pre) {
-        v.x = fmaxf(fmaf(v.x, pre[4 * q], pre[C + 4 * q]), 0.f);
-        v.y = fmaxf(fmaf(v.y, pre[4 * q + 1], pre[C + 4 * q + 1]), 0.f);
-        v.z = fmaxf(fmaf(v.z, pre[4 * q + 2], pre[C + 4 * q + 2]), 0.f);
-        v.w = fmaxf(fmaf(v.w, pre[4 * q + 3], pre[C + 4 * q + 3]), 0.f);
+  for (int jb = 0; jb < KB; ++jb) {
+    bs[jb] = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) acc[jb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int64_t pb = p0 + 4 * S * wave; pb < p1; pb += 16 * S) {
+    float4 a[S];
+    float zr[S][KB];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int64_t p = pb + 4 * s + lg;
+      a[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (p < p1 && col_ok) a[s] = *reinterpret_cast<const float4*>(f + p * ld_f + c0 + 4 * li);
+#pragma unroll
+      for (int jb = 0; jb < KB; ++jb) {
+        const int j = 16 * jb + li;
+        zr[s][jb] = (p < p1 && j < K) ? z[p * ld_z + j] : 0.f;
       }
-      *reinterpret_cast<float4*>(sf + r * C + 4 * q) = v;
     }
-    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < NO; ++k) {
-      const int o = t + k * kBlock;
-      if (o >= nout) break;
-      float a = acc[k];
-      if (o < K * C) {
-        const int j = o / C, c = o - j * C;
-        for (int r = 0; r < np; ++r) a = fmaf(sz[r * K + j], sf[r * C + c], a);
-      } else {
-        for (int r = 0; r < np; ++r) a += sz[r * K + (o - K * C)];
+    for (int s = 0; s < S; ++s) {
+      const float av[4] = {a[s].x, a[s].y, a[s].z, a[s].w};
+#pragma unroll
+      for (int jb = 0; jb < KB; ++jb) {
+        bs[jb] += zr[s][jb];
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+          acc[jb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(zr[s][jb], av[nb], acc[jb][nb], 0, 0, 0);
       }
-      acc[k] = a;
     }
   }
-  float* dst = part + static_cast<int64_t>(blockIdx.x) * nout;
+  // lane (i, g) of block (jb, nb) holds j = 16 jb + 4 g + r, c = c0 + 4 i + nb
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
 #pragma unroll
-  for (int k = 0; k < NO; ++k)
-    if (t + k * kBlock < nout) dst[t + k * kBlock] = acc[k];
+      for (int jb = 0; jb < KB; ++jb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          f32x4* d = reinterpret_cast<f32x4*>(&sum[(16 * jb + 4 * lg + r) * kLinCols + 4 * li]);
+          f32x4 v = f32x4{acc[jb][0][r], acc[jb][1][r], acc[jb][2][r], acc[jb][3][r]};
+          if (w > 0) v += *d;
+          *d = v;
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int jb = 0; jb < KB; ++jb) {
+    float v = bs[jb];
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if (lg == 0) sb[wave][16 * jb + li] = v;
+  }
+  __syncthreads();
+  float* dst = part + static_cast<int64_t>(blockIdx.x) * (static_cast<int64_t>(K) * C + K);
+  const int cols = min(kLinCols, C - c0);
+  for (int e = t; e < K * kLinCols; e += kBlock) {
+    const int j = e / kLinCols, c = e - j * kLinCols;
+    if (c < cols) dst[static_cast<int64_t>(j) * C + c0 + c] = sum[e];
+  }
+  if (blockIdx.y == 0)
+    for (int j = t; j < K; j += kBlock) dst[static_cast<int64_t>(K) * C + j] = (sb[0][j] + sb[1][j]) + (sb[2][j] + sb[3][j]);
 }
 
 // dW[j][c] (c < C_out, row stride C_out) and db[j]: sums over the chunks of
-// part[w][o], in chunk order.
+// part[w][o].  A workgroup takes 16 outputs; 16 slices of the chunks are
+// summed side by side (a thread walking all chunks of its output is a chain of
+// a thousand dependent adds) and then added in slice order.
 __global__ void __launch_bounds__(kBlock)
 k_lin_reduce(const float* __restrict__ part, int chunks, int K, int C, int C_out, float* __restrict__ dWc,
              float* __restrict__ dbc) {
+  __shared__ float sh[kLinRedSlices][kLinRedOut];
   const int nout = K * C + K;
-  const int o = blockIdx.x * kBlock + threadIdx.x;
-  if (o >= nout) return;
+  const int t = threadIdx.x, oi = t % kLinRedOut, sl = t / kLinRedOut;
+  const int o = blockIdx.x * kLinRedOut + oi;
   float a = 0.f;
-  for (int w = 0; w < chunks; ++w) a += part[static_cast<int64_t>(w) * nout + o];
+  if (o < nout)
+#pragma unroll 8
+    for (int w = sl; w < chunks; w += kLinRedSlices) a += part[static_cast<int64_t>(w) * nout + o];
+  sh[sl][oi] = a;
+  __syncthreads();
+  if (sl != 0 || o >= nout) return;
+  a = 0.f;
+#pragma unroll
+  for (int s = 0; s < kLinRedSlices; ++s) a += sh[s][oi];
   if (o < K * C) {
     const int j = o / C, c = o - j * C;
     if (dWc && c < C_out) dWc[j * C_out + c] = a;
@@ -367,9 +463,14 @@ k_lin_reduce(const float* __restrict__ part, int chunks, int K, int C, int C_out
   }
 }
 
-void cls_chunks(int64_t m, int64_t* chunk, int* chunks) {
-  int64_t c = std::max<int64_t>(kClsPts, (m + kClsMaxChunks - 1) / kClsMaxChunks);
-  c = (c + kClsPts - 1) / kClsPts * kClsPts;
+// Row chunks of k_lin_wgrad: enough for every compute unit (the column blocks
+// multiply them), fewer where the partials would outgrow what they are read
+// back for, and a multiple of the rows the four waves take in one step.
+void lin_chunks(int64_t m, int K, int C, int64_t* chunk, int* chunks) {
+  const int64_t nout = static_cast<int64_t>(K) * C + K;
+  const int64_t want = std::min<int64_t>(kLinMaxChunks, std::max<int64_t>(64, kLinMaxPartial / nout));
+  int64_t c = std::max<int64_t>(128, (m + want - 1) / want);
+  c = (c + 127) / 128 * 128;
   *chunk = c;
   *chunks = static_cast<int>(std::max<int64_t>(1, (m + c - 1) / c));
 }
@@ -434,51 +535,51 @@ namespace lat {
 int64_t classify_backward_partial_floats(int64_t m, int K, int C) {
   int64_t chunk;
   int chunks;
-  cls_chunks(m, &chunk, &chunks);
+  lin_chunks(m, K, C, &chunk, &chunks);
   return static_cast<int64_t>(chunks) * (static_cast<int64_t>(K) * C + K);
 }
 
 void launch_linear_backward(const float* z, int64_t ld_z, const float* W, int K, int C, int64_t m, const float* f,
-                            int64_t ld_f, const float* pre, float* df, int64_t ld_df, float* dW, int C_out, float* db,
-                            float* part, hipStream_t s) {
+                            int64_t ld_f, float* df, int64_t ld_df, float* dW, int C_out, float* db, float* part,
+                            hipStream_t s) {
+  const unsigned col_blocks = static_cast<unsigned>((C + kLinCols - 1) / kLinCols);
+  const int kb = (K + 15) / 16;   // K <= 64
+  auto by_kb = [&](auto go) {
+    if (kb <= 1) go(std::integral_constant<int, 1>{});
+    else if (kb == 2) go(std::integral_constant<int, 2>{});
+    else if (kb == 3) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
+  };
   if (df && m > 0) {
-    const int64_t b = (m * (C / 4) + kBlock - 1) / kBlock;
-    launch(k_lin_dinput, dim3(static_cast<unsigned>(std::min<int64_t>(b, 8192))), dim3(kBlock), 0, s, z, ld_z, W, K,
-           C, m, df, ld_df);
+    const unsigned gx = static_cast<unsigned>(std::min<int64_t>((m + 63) / 64, std::max(1u, 2048 / col_blocks)));
+    const bool v4 = K % 4 == 0 && ld_z % 4 == 0 && (reinterpret_cast<uintptr_t>(z) & 15u) == 0;
+    by_kb([&](auto kb_c) {
+      constexpr int KB = decltype(kb_c)::value;
+      if (v4)
+        launch((k_lin_dinput<KB, true>), dim3(gx, col_blocks), dim3(kBlock), 0, s, z, ld_z, W, K, C, m, df, ld_df);
+      else
+        launch((k_lin_dinput<KB, false>), dim3(gx, col_blocks), dim3(kBlock), 0, s, z, ld_z, W, K, C, m, df, ld_df);
+    });
   }
   if (!dW && !db) return;
   const int nout = K * C + K;
   int64_t chunk;
   int chunks;
-  cls_chunks(m, &chunk, &chunks);
-  if (m > 0) {
-    const size_t lds = sizeof(float) * kClsPts * static_cast<size_t>(K + C);
-    auto go = [&](auto no_c) {
-      constexpr int NO = decltype(no_c)::value;
-      static bool lds_limit_set = false;
-      if (!lds_limit_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lin_wgrad<NO>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  static_cast<int>(sizeof(float) * kClsPts * (64 + 512)));
-        lds_limit_set = true;
-      }
-      launch(k_lin_wgrad<NO>, dim3(static_cast<unsigned>(chunks)), dim3(kBlock), static_cast<uint32_t>(lds), s, z,
-             ld_z, f, ld_f, pre, K, C, m, chunk, part);
-    };
-    const int no = (nout + kBlock - 1) / kBlock;
-    if (no <= 2) go(std::integral_constant<int, 2>{});
-    else if (no <= 8) go(std::integral_constant<int, 8>{});
-    else if (no <= 24) go(std::integral_constant<int, 24>{});
-    else go(std::integral_constant<int, 65>{});
-  }
-  launch(k_lin_reduce, dim3(static_cast<unsigned>((nout + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+  lin_chunks(m, K, C, &chunk, &chunks);
+  if (m > 0)
+    by_kb([&](auto kb_c) {
+      constexpr int KB = decltype(kb_c)::value;
+      launch(k_lin_wgrad<KB>, dim3(static_cast<unsigned>(chunks), col_blocks), dim3(kBlock), 0, s, z, ld_z, f, ld_f,
+             K, C, m, chunk, part);
+    });
+  launch(k_lin_reduce, dim3(static_cast<unsigned>((nout + kLinRedOut - 1) / kLinRedOut)), dim3(kBlock), 0, s,
          static_cast<const float*>(part), m > 0 ? chunks : 0, K, C, C_out, dW, db);
 }
 
 void launch_classify_backward(const float* z, int64_t ld_z, const float* Wc, int K, int C, int64_t m, const float* f,
                               float* df, float* dWc, float* dbc, float* part, hipStream_t s) {
   ScopedKernelTimer tm("classify_bwd", s);
-  launch_linear_backward(z, ld_z, Wc, K, C, m, f, C, nullptr, df, C, dWc, C, dbc, part, s);
+  launch_linear_backward(z, ld_z, Wc, K, C, m, f, C, df, C, dWc, C, dbc, part, s);
 }
 
 }  // namespace lat

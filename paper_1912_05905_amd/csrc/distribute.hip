@@ -1143,7 +1143,7 @@ void launch_distribute_backward(const int32_t* offsets, const int32_t* entries, 
   for (int i = 2; i >= 0; --i) {
     // dA = g W_i, dW_i, db_i on the activations; then dH_i = GroupNorm +
     // ReLU backward of dA
-    launch_linear_backward(g, co[i], Ws[i], co[i], ci[i], total, A32[i], ci[i], nullptr, gA, ci[i], dWs[i], wout[i],
+    launch_linear_backward(g, co[i], Ws[i], co[i], ci[i], total, A32[i], ci[i], gA, ci[i], dWs[i], wout[i],
                            dbs[i], part, s);
     launch_gn_backward(Xh32[i], ci[i], gA, ci[i], ci[i], groups(ci[i]), total, gam[i], nullptr, stats[i], dgam[i],
                        dbet[i], coef, gB, ci[i], gnw, s, A32[i], ci[i], true);

@@ -320,14 +320,14 @@ void launch_gn_affine(const void* x, int64_t ld, int C, int bf16, int64_t n, int
 // z (either may be NULL); part holds classify_backward_partial_floats
 int64_t classify_backward_partial_floats(int64_t m, int K, int C);
 // backward of out_p = W a_p + b over m rows (W: K x C [out][in], dense, 16-byte
-// aligned, C a multiple of 4) for z = dL/dout (m x K, row stride ld_z):
-// df = z W (m x C, row stride ld_df; NULL: skipped), dW = z^T a written as
-// K x C_out (the first C_out columns), db = column sums of z (either NULL:
-// skipped).  a = f (row stride ld_f), or max(f scale + shift, 0) with pre =
-// [C scales][C shifts].  part holds classify_backward_partial_floats(m, K, C).
+// aligned, K <= 64, C a multiple of 4) for z = dL/dout (m x K, row stride
+// ld_z): df = z W (m x C, row stride ld_df; NULL: skipped), dW = z^T a written
+// as K x C_out (the first C_out columns), db = column sums of z (either NULL:
+// skipped).  a = f (row stride ld_f, a multiple of 4).  part holds
+// classify_backward_partial_floats(m, K, C).
 void launch_linear_backward(const float* z, int64_t ld_z, const float* W, int K, int C, int64_t m, const float* f,
-                            int64_t ld_f, const float* pre, float* df, int64_t ld_df, float* dW, int C_out, float* db,
-                            float* part, hipStream_t s);
+                            int64_t ld_f, float* df, int64_t ld_df, float* dW, int C_out, float* db, float* part,
+                            hipStream_t s);
 void launch_classify_backward(const float* z, int64_t ld_z, const float* Wc, int K, int C, int64_t m, const float* f,
                               float* df, float* dWc, float* dbc, float* part, hipStream_t s);
 // a = max(x pre[c] + pre[C + c], 0) for fp32 x (n x C), the pre-activated
