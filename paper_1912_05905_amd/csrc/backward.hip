@@ -111,117 +111,232 @@ k_conv_bwd_prep(const void* __restrict__ dY, int64_t ld_dy, const void* __restri
 }
 
 // dW[t][o][i] = sum_v G[v][o] X[nb(v,t)][i] as a GEMM with the vertices as
-// the reduction dimension: A = G^T (Cout x K), B = the gathered rows
-// (K x Cin); bf16 G and X are widened to fp32 as they are staged.  A workgroup owns one tap, one 64 x 64 tile of (o, i) and one
-// chunk of V vertices; it stages 32 vertices at a time (G rows and gathered
-// X rows, a missing neighbour reads as zeros) in double-buffered LDS, each
-// wave multiplying a 32 x 32 sub-tile on v_mfma_f32_16x16x4_f32.  Partials
-// go to part[chunk][tap][o][i]; the workgroups of tap 0 and the first i
-// tile also sum the G columns (the bias gradient).
+// the reduction dimension: A = G^T, B = the gathered rows.  A workgroup owns
+// one tap, one 64 x 64 tile of (o, i) and one chunk of V vertices, a quarter
+// of it per wave, and each wave multiplies whole 64 x 64 tiles with operands
+// loaded straight into the MFMA layout: lane (i, g) loads the 4 channels 4 i
+// .. 4 i + 3 of the rows its lane group g stands for, which serve four
+// products whose row (or column) i stands for channel 4 i + e.
+//   fp32: a step is 16 vertices, v_mfma_f32_16x16x4_f32, 16-byte loads;
+//   bf16: a step is 32 vertices, v_mfma_f32_16x16x32_bf16 (bf16 products are
+//         exact in fp32 and are summed in fp32); a lane's 8 rows x 4 channels
+//         are turned into 8 rows per channel by byte permutes.
+// Only vertices that have the tap are multiplied: a wave compacts 64 table
+// entries at a time into a ring of (v, nb) pairs in LDS and takes full steps
+// from it (on rooms and scans a quarter to a half of the pairs are missing).
+// The four waves are added in wave order into part[chunk][tap][o][i].
+// The workgroups of blockIdx.y = 0 sum the G columns (the bias gradient).
+// Staging both operands in LDS, bf16 widened to fp32, the weight gradient took
+// 1191 us at 128 x 128 bf16 on a 212k-vertex level and 23 us at 64 x 64 fp32 on
+// the 16k vertices of a LiDAR scan; here 143 and 21 us.
 constexpr int kWgTile = 64;
-constexpr int kWgStage = 32;
-constexpr int kWgPitch = kWgTile + 4;
+constexpr int kWgRing = 256;                 // (v, nb) pairs a wave can hold, a power of two
+constexpr int kWgTargetBlocks = 768;         // three workgroups per compute unit over taps, tiles and chunks
+
+template <bool BF16> struct WgRow;
+template <> struct WgRow<false> {
+  static constexpr int kStep = 16, kPer = 4;   // vertices per step, rows of it per lane
+  float4 v;
+  __device__ inline void load(const void* base, int64_t at) {
+    v = *reinterpret_cast<const float4*>(static_cast<const float*>(base) + at);
+  }
+  __device__ inline void zero() { v = make_float4(0.f, 0.f, 0.f, 0.f); }
+};
+template <> struct WgRow<true> {
+  static constexpr int kStep = 32, kPer = 8;
+  uint2 v;
+  __device__ inline void load(const void* base, int64_t at) {
+    v = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(base) + at);
+  }
+  __device__ inline void zero() { v = make_uint2(0u, 0u); }
+};
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// The bf16 values of channel e of a lane's 8 rows, in row order.
+template <int e>
+__device__ inline bf16x8 wg_channel(const WgRow<true> (&r)[8]) {
+  constexpr uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+  u32x4 o;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    o[q] = __builtin_amdgcn_perm(e < 2 ? r[2 * q + 1].v.x : r[2 * q + 1].v.y, e < 2 ? r[2 * q].v.x : r[2 * q].v.y, sel);
+  return __builtin_bit_cast(bf16x8, o);
+}
+
+__device__ inline void wg_mma(f32x4 (&acc)[4][4], const WgRow<true> (&g)[8], const WgRow<true> (&x)[8]) {
+  const bf16x8 a[4] = {wg_channel<0>(g), wg_channel<1>(g), wg_channel<2>(g), wg_channel<3>(g)};
+  const bf16x8 b[4] = {wg_channel<0>(x), wg_channel<1>(x), wg_channel<2>(x), wg_channel<3>(x)};
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int f = 0; f < 4; ++f) acc[e][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[e], b[f], acc[e][f], 0, 0, 0);
+}
+__device__ inline void wg_mma(f32x4 (&acc)[4][4], const WgRow<false> (&g)[4], const WgRow<false> (&x)[4]) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const float a[4] = {g[s].v.x, g[s].v.y, g[s].v.z, g[s].v.w};
+    const float b[4] = {x[s].v.x, x[s].v.y, x[s].v.z, x[s].v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int f = 0; f < 4; ++f) acc[e][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[f], acc[e][f], 0, 0, 0);
+  }
+}
 
 template <bool BF16>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, 2)
 k_conv_wgrad(const int32_t* __restrict__ nbr, int64_t ldn, int64_t n_out, int64_t V, const void* __restrict__ X,
              int64_t ld_x, int Cin, const void* __restrict__ G, int64_t ld_g, int Cout, int tiles_i,
              float* __restrict__ part, float* __restrict__ part_b) {
-  __shared__ __align__(16) float Gs[2][kWgStage][kWgPitch];
-  __shared__ __align__(16) float Xs[2][kWgStage][kWgPitch];
+  using Row = WgRow<BF16>;
+  constexpr int S = Row::kStep, NR = Row::kPer;
+  __shared__ __align__(16) int2 ring_s[4][kWgRing];
+  __shared__ __align__(16) float sum[kWgTile * kWgTile];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int li = lane & 15, lg = lane >> 4;
   const int64_t chunk = blockIdx.x;
-  const int tap = blockIdx.y;
   const int ti = static_cast<int>(blockIdx.z) % tiles_i, to = static_cast<int>(blockIdx.z) / tiles_i;
   const int o0 = to * kWgTile, i0 = ti * kWgTile;
-  const int64_t v_begin = chunk * V, v_end = min(v_begin + V, n_out);
-  const int wo = (wave >> 1) * 32, wi = (wave & 1) * 32;
-  const bool do_bias = part_b != nullptr && tap == 0 && ti == 0;
-  const int lr = t >> 4, lc = 4 * (t & 15);   // rows lr and lr + 16, columns lc..lc+3 of a stage
-  const int32_t* tab = nbr + static_cast<int64_t>(tap) * ldn;
+  const int64_t c_begin = chunk * V, c_end = min(c_begin + V, n_out);
 
-  float4 ga[2], xa[2];
-  auto load = [&](int64_t vb) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int64_t v = vb + lr + 16 * h;
-      float4 g = make_float4(0.f, 0.f, 0.f, 0.f), x = g;
-      if (v < v_end) {
-        if (o0 + lc < Cout) g = load4<BF16>(G, v * ld_g + o0 + lc);
-        const int32_t u = tab[v];
-        if (u >= 0 && i0 + lc < Cin) x = load4<BF16>(X, static_cast<int64_t>(u) * ld_x + i0 + lc);
-      }
-      ga[h] = g;
-      xa[h] = x;
-    }
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      *reinterpret_cast<float4*>(&Gs[buf][lr + 16 * h][lc]) = ga[h];
-      *reinterpret_cast<float4*>(&Xs[buf][lr + 16 * h][lc]) = xa[h];
-    }
-  };
-
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float bsum = 0.f;
-
-  load(v_begin);
-  store(0);
-  __syncthreads();
-  int buf = 0;
-  for (int64_t vb = v_begin; vb < v_end; vb += kWgStage) {
-    const bool more = vb + kWgStage < v_end;
-    if (more) load(vb + kWgStage);
-#pragma unroll
-    for (int ks = 0; ks < kWgStage / 4; ++ks) {
-      float a[2], b[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        a[h] = Gs[buf][4 * ks + lg][wo + 16 * h + li];
-        b[h] = Xs[buf][4 * ks + lg][wi + 16 * h + li];
-      }
-#pragma unroll
-      for (int ao = 0; ao < 2; ++ao)
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi) acc[ao][bi] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ao], b[bi], acc[ao][bi], 0, 0, 0);
-    }
-    if (do_bias && t < kWgTile)
+  if (blockIdx.y == 0) {
+    // bias: the column sums of G over the chunk (16 rows side by side)
+    if (part_b == nullptr || ti != 0) return;
+    const int lr = t >> 4, lc = 4 * (t & 15);
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (o0 + lc < Cout)
 #pragma unroll 8
-      for (int r = 0; r < kWgStage; ++r) bsum += Gs[buf][r][t];
-    if (more) store(buf ^ 1);
+      for (int64_t v = c_begin + lr; v < c_end; v += 16) {
+        const float4 g = load4<BF16>(G, v * ld_g + o0 + lc);
+        a.x += g.x; a.y += g.y; a.z += g.z; a.w += g.w;
+      }
+    *reinterpret_cast<float4*>(&sum[lr * kWgTile + lc]) = a;
     __syncthreads();
-    buf ^= 1;
+    if (t < kWgTile && o0 + t < Cout) {
+      float s = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s += sum[r * kWgTile + t];
+      part_b[chunk * Cout + o0 + t] = s;
+    }
+    return;
+  }
+  const int tap = blockIdx.y - 1;
+  const int32_t* tab = nbr + static_cast<int64_t>(tap) * ldn;
+  int2* ring = ring_s[wave];
+  // the wave's vertices; columns past the matrix read its last ones (their
+  // products are not written)
+  const int64_t sub = (V + 3) / 4;
+  int64_t vb = min(c_begin + wave * sub, c_end);
+  const int64_t v_end = min(vb + sub, c_end);
+  const int64_t oc = min(o0 + 4 * li, Cout - 4), ic = min(i0 + 4 * li, Cin - 4);
+
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int f = 0; f < 4; ++f) acc[e][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  uint32_t head = 0, tail = 0;   // pairs taken from and put into the ring
+  int32_t un = vb + lane < v_end ? tab[vb + lane] : -1;
+  // pairs of the next 64 vertices into the ring until it holds a step
+  auto fill = [&]() {
+    while (tail - head < static_cast<uint32_t>(S) && vb < v_end) {
+      const int32_t u = un;
+      const int32_t v = static_cast<int32_t>(vb) + lane;
+      const uint64_t has = __ballot(u >= 0);
+      vb += 64;
+      un = vb + lane < v_end ? tab[vb + lane] : -1;
+      const uint32_t at = __builtin_popcountll(has & ((uint64_t{1} << lane) - 1));
+      if (u >= 0) ring[(tail + at) & (kWgRing - 1)] = make_int2(v, u);
+      tail += __builtin_popcountll(has);
+    }
+    // a wave's LDS accesses take effect in order; the fences keep the
+    // compiler from moving the reads above the writes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  auto fetch = [&](Row (&g)[NR], Row (&x)[NR], uint32_t count) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const uint32_t e = static_cast<uint32_t>(NR * lg + r);
+      if (e < count) {
+        const int2 p = ring[(head + e) & (kWgRing - 1)];
+        g[r].load(G, static_cast<int64_t>(p.x) * ld_g + oc);
+        x[r].load(X, static_cast<int64_t>(p.y) * ld_x + ic);
+      } else {
+        g[r].zero();
+        x[r].zero();
+      }
+    }
+  };
+  Row ga[NR], xa[NR], gb[NR], xb[NR];
+  fill();
+  bool more = tail - head >= static_cast<uint32_t>(S);
+  if (more) {
+    fetch(ga, xa, S);
+    head += S;
+  }
+  // the rows of a step are loaded while the step before is multiplied
+  auto step = [&](Row (&g)[NR], Row (&x)[NR], Row (&gn)[NR], Row (&xn)[NR]) {
+    fill();
+    const bool next = tail - head >= static_cast<uint32_t>(S);
+    if (next) {
+      fetch(gn, xn, S);
+      head += S;
+    }
+    wg_mma(acc, g, x);
+    return next;
+  };
+  while (more) {
+    more = step(ga, xa, gb, xb);
+    if (!more) break;
+    more = step(gb, xb, ga, xa);
+  }
+  if (tail != head) {
+    fetch(ga, xa, tail - head);
+    wg_mma(acc, ga, xa);
   }
 
-  // lane (i, g) of block (ao, bi) holds o = 16 ao + 4 g + r, i = 16 bi + i
+  // lane (i, g) of product (e, f) holds o = 4 (4 g + r) + e, i = 4 i + f
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          f32x4* d = reinterpret_cast<f32x4*>(&sum[(16 * lg + 4 * r + e) * kWgTile + 4 * li]);
+          f32x4 v = f32x4{acc[e][0][r], acc[e][1][r], acc[e][2][r], acc[e][3][r]};
+          if (w > 0) v += *d;
+          *d = v;
+        }
+    }
+    __syncthreads();
+  }
   float* P = part + (chunk * 9 + tap) * static_cast<int64_t>(Cout) * Cin;
-#pragma unroll
-  for (int ao = 0; ao < 2; ++ao)
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int o = o0 + wo + 16 * ao + 4 * lg + r, i = i0 + wi + 16 * bi + li;
-        if (o < Cout && i < Cin) P[static_cast<int64_t>(o) * Cin + i] = acc[ao][bi][r];
-      }
-  if (do_bias && t < kWgTile && o0 + t < Cout) part_b[chunk * Cout + o0 + t] = bsum;
+  for (int q = t; q < kWgTile * kWgTile / 4; q += kBlock) {
+    const int o = o0 + q / (kWgTile / 4), i = i0 + 4 * (q % (kWgTile / 4));
+    if (o < Cout && i < Cin)
+      *reinterpret_cast<f32x4*>(P + static_cast<int64_t>(o) * Cin + i) = *reinterpret_cast<const f32x4*>(&sum[4 * q]);
+  }
 }
 
-// dW = sum over chunks of the partials, dbias likewise; fixed order.  A
-// thread sums 4 consecutive entries (count and Cout are multiples of 4).
+// dW = sum over chunks of the partials, dbias likewise; fixed order: a
+// workgroup takes 64 groups of 4 consecutive entries (count and Cout are
+// multiples of 4), four slices of the chunks are summed side by side and added
+// in slice order.
+constexpr int kWgRedSlices = 4, kWgRedQuads = kBlock / kWgRedSlices;
+
 __global__ void __launch_bounds__(kBlock)
 k_wgrad_reduce(const float* __restrict__ part, const float* __restrict__ part_b, int64_t chunks, int64_t count,
                int Cout, float* __restrict__ dW, float* __restrict__ dbias) {
-  const int64_t q = 4 * (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x);
-  const float* src;
-  int64_t stride;
-  float* dst;
+  __shared__ f32x4 sh[kWgRedSlices][kWgRedQuads];
+  const int qi = threadIdx.x % kWgRedQuads, sl = threadIdx.x / kWgRedQuads;
+  const int64_t q = 4 * (static_cast<int64_t>(blockIdx.x) * kWgRedQuads + qi);
+  const float* src = nullptr;
+  int64_t stride = 0;
+  float* dst = nullptr;
   if (q < count) {
     src = part + q;
     stride = count;
@@ -230,36 +345,34 @@ k_wgrad_reduce(const float* __restrict__ part, const float* __restrict__ part_b,
     src = part_b + (q - count);
     stride = Cout;
     dst = dbias ? dbias + (q - count) : nullptr;
-  } else {
-    return;
   }
-  if (!dst) return;
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-  for (int64_t c = 0; c < chunks; ++c) {
-    const float4 x = *reinterpret_cast<const float4*>(src + c * stride);
-    a.x += x.x;
-    a.y += x.y;
-    a.z += x.z;
-    a.w += x.w;
-  }
-  *reinterpret_cast<float4*>(dst) = a;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  if (dst)
+#pragma unroll 8
+    for (int64_t c = sl; c < chunks; c += kWgRedSlices) a += *reinterpret_cast<const f32x4*>(src + c * stride);
+  sh[sl][qi] = a;
+  __syncthreads();
+  if (sl != 0 || !dst) return;
+#pragma unroll
+  for (int k = 1; k < kWgRedSlices; ++k) a += sh[k][qi];
+  *reinterpret_cast<f32x4*>(dst) = a;
 }
 
 inline unsigned blocks_for(int64_t threads) { return static_cast<unsigned>((threads + kBlock - 1) / kBlock); }
 
-// Vertex chunks of the weight gradient: about two workgroups per compute
-// unit over taps and tiles (more chunks would only grow the partials the
-// reduction reads), chunks a multiple of the stage.
+// Vertex chunks of the weight gradient: three workgroups per compute unit
+// over taps and tiles (more chunks would only grow the partials the reduction
+// reads), in multiples of 8 so that the taps of a chunk, which gather the same
+// rows, run on one XCD (workgroup b runs on XCD b % 8), and at least 64
+// vertices each.
 void wgrad_chunks(int64_t n_out, int tiles, int64_t* chunks, int64_t* V) {
-  int64_t want = std::max<int64_t>(1, 512 / (9 * static_cast<int64_t>(tiles)));
-  want = std::min<int64_t>(want, (n_out + kWgStage - 1) / kWgStage);
+  int64_t want = std::max<int64_t>(8, (kWgTargetBlocks / (9 * static_cast<int64_t>(tiles)) + 7) / 8 * 8);
+  want = std::min<int64_t>(want, (n_out + 63) / 64);
   int64_t v = (n_out + want - 1) / want;
-  v = (v + kWgStage - 1) / kWgStage * kWgStage;
+  v = (v + 63) / 64 * 64;
   *V = v;
   *chunks = (n_out + v - 1) / v;
 }
-
 
 // ---- linear layers backward (the classifier fused with DeformSlice, the
 // 1x1 layers of Distribute + PointNet) ----
@@ -515,7 +628,8 @@ void launch_conv_wgrad(const int32_t* nbr, int64_t ldn, int64_t n_out, const voi
   float* part = partials;
   float* part_b = dbias ? partials + chunks * count : nullptr;
   if (chunks > 0) {
-    const dim3 grid(static_cast<unsigned>(chunks), 9, static_cast<unsigned>(tiles_o * tiles_i));
+    // blockIdx.y: the bias, then the taps
+    const dim3 grid(static_cast<unsigned>(chunks), dW ? 10 : 1, static_cast<unsigned>(tiles_o * tiles_i));
     if (bf16)
       launch(k_conv_wgrad<true>, grid, dim3(kBlock), 0, s, nbr, ldn, n_out, V, X, ld_x, Cin, G, ld_g, Cout, tiles_i,
              part, part_b);
@@ -524,7 +638,7 @@ void launch_conv_wgrad(const int32_t* nbr, int64_t ldn, int64_t n_out, const voi
              part, part_b);
   }
   // with no output vertex (chunks = 0) the sums below are zero
-  launch(k_wgrad_reduce, dim3(blocks_for((count + Cout) / 4)), dim3(kBlock), 0, s, static_cast<const float*>(part),
+  launch(k_wgrad_reduce, dim3(static_cast<unsigned>(((count + Cout) / 4 + kWgRedQuads - 1) / kWgRedQuads)), dim3(kBlock), 0, s, static_cast<const float*>(part),
          static_cast<const float*>(part_b), chunks, count, Cout, dW, dbias);
 }
 

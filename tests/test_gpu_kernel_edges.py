@@ -29,3 +29,27 @@ def test_linear_backward_tiles(L, O, m, C, K):  # noqa: F811
     P.assert_close(P.rows_in_oracle_order(_host(got[0]), g2o), ref[0], P.TOL_F32, f"dX m={m} C={C} K={K}")
     P.assert_close(_host(got[3]), ref[3], P.TOL_F32, f"dWc m={m} C={C} K={K}")
     P.assert_close(_host(got[4]), ref[4], P.TOL_F32, f"dbc m={m} C={C} K={K}")
+
+
+# weight gradient: 64 x 64 tiles, steps of 16 (fp32) and 32 (bf16) vertices, chunks of 64, missing taps
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,cin,cout", [(1, 8, 8), (9, 64, 72), (65, 56, 64), (700, 136, 128), (3000, 24, 200)])
+def test_weight_gradient_tiles(L, O, m, cin, cout, dtype):  # noqa: F811
+    gl, ol, g2o = _pair(L, O, _cloud(2100 + m, m, 0.7), 0.07)
+    gc, oc = gl.coarsen(), ol.coarsen()
+    g2o_c = P.key_permutation(_host(gc.keys()), oc.keys())
+    rng = np.random.default_rng(m)
+    rnd = O.round_bf16 if dtype == "bf16" else (lambda a: a.astype(np.float32))
+    dev = (lambda a: _dev(a.astype(np.float32), torch.bfloat16)) if dtype == "bf16" else _dev
+    for gd, gs, od, os_, pd, ps in ((gl, gl, ol, ol, g2o, g2o), (gc, gl, oc, ol, g2o_c, g2o), (gl, gc, ol, oc, g2o, g2o_c)):
+        X = rnd(rng.normal(size=(os_.n, cin)))
+        dY = rnd(rng.normal(size=(od.n, cout)))
+        W = np.zeros((9, cin, cout))
+        _, odw, odb = od.conv_backward(os_, X.astype(np.float64), W, dY.astype(np.float64))
+        fn = gd.conv_backward_bf16 if dtype == "bf16" else gd.conv_backward
+        _, gdw, gdb = fn(gs, dev(X[ps]), None, dev(dY[pd]), want_dx=False)
+        P.assert_close(np.transpose(_host(gdw), (0, 2, 1)), odw, P.TOL_F32, f"dW m={m} {cin}->{cout} {dtype}")
+        P.assert_close(_host(gdb), odb, P.TOL_F32, f"dbias m={m} {cin}->{cout} {dtype}")
+        _, none, gdb = fn(gs, dev(X[ps]), None, dev(dY[pd]), want_dx=False, want_dw=False)
+        assert none is None
+        P.assert_close(_host(gdb), odb, P.TOL_F32, f"dbias alone m={m} {cin}->{cout} {dtype}")
