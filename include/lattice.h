@@ -499,8 +499,8 @@ int lattice_deform_slice_classify_backward(lattice_t L, const float* vals_dev, i
  *   lattice_conv_preact_backward, statistics over all rows) gives dh_{i-1}
  *   and the normalisation's dgamma / dbeta;
  *   dfeat_p = sum over the d+1 rows of point p of the feature part of dh_0.
- * The forward is recomputed in float32 (every block's input kept in the
- * work space); positions are inputs and get no gradient.
+ * The forward is recomputed in float64 (every block's input kept in float32 in
+ * the work space); positions are inputs and get no gradient.
  *   Arguments pos_dev .. C3 as for lattice_distribute_pointnet (W2_dev and
  *   W3_dev 16-byte aligned).
  *   dfeat_dev  m x Cf float32, row stride ld_dfeat (0 = Cf), or NULL.
@@ -509,7 +509,7 @@ int lattice_deform_slice_classify_backward(lattice_t L, const float* vals_dev, i
  *   dgamma_dev, dbeta_dev  (d + Cf) + C1 + C2 floats each (the layout of
  *              gn_gamma_dev), or NULL.
  * Sums over rows run in a fixed order.  Uses work space of about
- * 4 m ((d + Cf) + C1 + C2 + 4 max width) floats from the pool.
+ * 4 m (2 ((d + Cf) + C1 + C2) + 2 max width) floats from the pool.
  */
 int lattice_distribute_pointnet_backward(lattice_t L, const float* pos_dev, const float* feat_dev, int64_t ld_feat,
                                          int Cf, const float* gn_gamma_dev, const float* gn_beta_dev, float eps,

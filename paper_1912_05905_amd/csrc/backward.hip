@@ -386,20 +386,72 @@ void wgrad_chunks(int64_t n_out, int tiles, int64_t* chunks, int64_t* V) {
 // passes are bound by the rows' memory traffic.  At 480,000 rows, K = 64, C =
 // 32 (the last PointNet layer of a LiDAR scan) they took 192 (dA), 279 (dW)
 // and 239 us (the partials, one thread per output over 1,000 of them) as FMA
-// loops, and 62, 76 and 6 us here; at 200,000 rows, K = 20, C = 128 (the head of
-// a room) 91, 147 and 215 us, and 38, 38 and 6 us here.
+// loops, and 63 (dA), 92 (dW) and 6 us here with the maxima's rows routed on
+// the fly; at 200,000 rows, K = 20, C = 128 (the head of a room) 91, 147 and 215
+// us, and 38, 38 and 6 us here.
 constexpr int kLinCols = 64;        // columns of C per workgroup
 constexpr int kLinMaxChunks = 1024;
 constexpr int64_t kLinMaxPartial = 4 << 20;   // floats of partials aimed at
 constexpr int kLinRedOut = 16, kLinRedSlices = kBlock / kLinRedOut;
 
+// The rows z_p: given, or dL/dx of the maximum over a vertex's list routed to
+// its rows: row p of vertex v = ev[p] holds dX[v][j] where p is the row of
+// channel j's maximum (am), else 0.  get<N>(key(p), p, j, o) is o = z_p[j .. j
+// + N - 1], j a multiple of N, entries past K being 0; the key is loaded ahead.
+// V4: rows of z allow 16-byte loads.
+template <bool V4>
+struct GivenRows {
+  const float* z;
+  int64_t ld;
+  int K;
+  __device__ inline int32_t key(int64_t) const { return 0; }
+  template <int N>
+  __device__ inline void get(int32_t, int64_t p, int j, float (&o)[N]) const {
+    const float* r = z + p * ld + j;
+    if constexpr (V4 && N == 4) {
+      const float4 v = *reinterpret_cast<const float4*>(r);
+      o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+    } else if constexpr (V4 && N == 2) {
+      const float2 v = *reinterpret_cast<const float2*>(r);
+      o[0] = v.x; o[1] = v.y;
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; ++e) o[e] = j + e < K ? r[e] : 0.f;
+    }
+  }
+};
+struct RoutedRows {
+  const int32_t* ev;
+  const int32_t* am;
+  const float* dX;
+  int64_t ld;
+  int K;
+  __device__ inline int32_t key(int64_t p) const { return ev[p]; }
+  template <int N>
+  __device__ inline void get(int32_t v, int64_t p, int j, float (&o)[N]) const {
+    const int32_t* a = am + static_cast<int64_t>(v) * K + j;
+    const float* d = dX + static_cast<int64_t>(v) * ld + j;
+    const int32_t r = static_cast<int32_t>(p);
+    if constexpr (N == 4) {
+      const int4 av = *reinterpret_cast<const int4*>(a);
+      const float4 dv = *reinterpret_cast<const float4*>(d);
+      o[0] = av.x == r ? dv.x : 0.f;
+      o[1] = av.y == r ? dv.y : 0.f;
+      o[2] = av.z == r ? dv.z : 0.f;
+      o[3] = av.w == r ? dv.w : 0.f;
+    } else {
+#pragma unroll
+      for (int e = 0; e < N; ++e) o[e] = j + e < K && a[e] == r ? d[e] : 0.f;
+    }
+  }
+};
+
 // dA (m x C): 16 rows a step and wave.  A = W^T (LDS, fragment order), B = z^T:
 // lane (i, g) holds z[p0 + i][16 jb + 4 g + s] for step s of block jb, and
-// receives dA[p0 + i][c0 + 16 nb + 4 g + r].  V4: rows of z allow 16-byte loads.
-template <int KB, bool V4>
+// receives dA[p0 + i][c0 + 16 nb + 4 g + r].
+template <int KB, class Rows>
 __global__ void __launch_bounds__(kBlock)
-k_lin_dinput(const float* __restrict__ z, int64_t ld_z, const float* __restrict__ W, int K, int C, int64_t m,
-             float* __restrict__ df, int64_t ld_df) {
+k_lin_dinput(Rows rows, const float* __restrict__ W, int K, int C, int64_t m, float* __restrict__ df, int64_t ld_df) {
   __shared__ __align__(16) float ws[KB * 4 * 64 * 4];   // [jb][nb][lane][s]
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int li = lane & 15, lg = lane >> 4;
@@ -413,26 +465,31 @@ k_lin_dinput(const float* __restrict__ z, int64_t ld_z, const float* __restrict_
   const int64_t groups = (m + 15) / 16;
   const f32x4* wf = reinterpret_cast<const f32x4*>(ws) + lane;
   const int64_t step = static_cast<int64_t>(gridDim.x) * 4;
-  auto load = [&](int64_t grp, float (&zr)[KB][4]) {
+  // past the last row: zeros, no access
+  auto load_key = [&](int64_t grp) {
+    const int64_t p = grp * 16 + li;
+    return p < m ? rows.key(p) : 0;
+  };
+  auto load = [&](int64_t grp, int32_t key, float (&zr)[KB][4]) {
     const int64_t p = grp * 16 + li;
 #pragma unroll
     for (int jb = 0; jb < KB; ++jb) {
       const int j = 16 * jb + 4 * lg;
-      if constexpr (V4) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (p < m && j < K) v = *reinterpret_cast<const float4*>(z + p * ld_z + j);
-        zr[jb][0] = v.x; zr[jb][1] = v.y; zr[jb][2] = v.z; zr[jb][3] = v.w;
-      } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) zr[jb][s] = (p < m && j + s < K) ? z[p * ld_z + j + s] : 0.f;
-      }
+      for (int s = 0; s < 4; ++s) zr[jb][s] = 0.f;
+      if (p < m && j < K) rows.get(key, p, j, zr[jb]);
     }
   };
   float zc[KB][4], zn[KB][4];
   int64_t grp = static_cast<int64_t>(blockIdx.x) * 4 + wave;
-  if (grp < groups) load(grp, zc);
+  int32_t key = 0;
+  if (grp < groups) {
+    load(grp, load_key(grp), zc);
+    key = load_key(grp + step);
+  }
   for (; grp < groups; grp += step) {
-    load(grp + step, zn);   // past the last row: zeros, no access
+    load(grp + step, key, zn);
+    key = load_key(grp + 2 * step);
     f32x4 acc[4];
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -463,14 +520,14 @@ k_lin_dinput(const float* __restrict__ z, int64_t ld_z, const float* __restrict_
 
 // Workgroup (w, cb): over chunk w of the rows, part[w][j C + c] = sum_p z_pj
 // a_pc for the columns of block cb, and for cb = 0 part[w][K C + j] = sum_p
-// z_pj.  A = z^T: lane (i, g) holds z[p + g][16 jb + i]; B = a: the lane's
-// float4 a[p + g][c0 + 4 i ..] feeds four products whose column i stands for
-// c0 + 4 i + nb.  The four waves take 16 rows each in turn and are added in
+// z_pj.  A = z^T: lane (i, g) holds z[p + g][KB i + jb] for block jb; B = a: the
+// lane's float4 a[p + g][c0 + 4 i ..] feeds four products whose column i stands
+// for c0 + 4 i + nb.  The four waves take 16 rows each in turn and are added in
 // wave order.
-template <int KB>
+template <int KB, class Rows>
 __global__ void __launch_bounds__(kBlock)
-k_lin_wgrad(const float* __restrict__ z, int64_t ld_z, const float* __restrict__ f, int64_t ld_f, int K, int C,
-            int64_t m, int64_t chunk, float* __restrict__ part) {
+k_lin_wgrad(Rows rows, const float* __restrict__ f, int64_t ld_f, int K, int C, int64_t m, int64_t chunk,
+            float* __restrict__ part) {
   __shared__ float sum[KB * 16 * kLinCols];   // [j][c]
   __shared__ float sb[4][KB * 16];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -488,6 +545,16 @@ k_lin_wgrad(const float* __restrict__ z, int64_t ld_z, const float* __restrict__
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) acc[jb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
+  int32_t key[S];
+  auto load_keys = [&](int64_t pb) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int64_t p = pb + 4 * s + lg;
+      key[s] = p < p1 ? rows.key(p) : 0;
+    }
+  };
+  const int j0 = KB * li;   // the lane's columns of z
+  load_keys(p0 + 4 * S * wave);
   for (int64_t pb = p0 + 4 * S * wave; pb < p1; pb += 16 * S) {
     float4 a[S];
     float zr[S][KB];
@@ -497,11 +564,10 @@ k_lin_wgrad(const float* __restrict__ z, int64_t ld_z, const float* __restrict__
       a[s] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (p < p1 && col_ok) a[s] = *reinterpret_cast<const float4*>(f + p * ld_f + c0 + 4 * li);
 #pragma unroll
-      for (int jb = 0; jb < KB; ++jb) {
-        const int j = 16 * jb + li;
-        zr[s][jb] = (p < p1 && j < K) ? z[p * ld_z + j] : 0.f;
-      }
+      for (int jb = 0; jb < KB; ++jb) zr[s][jb] = 0.f;
+      if (p < p1 && j0 < K) rows.get(key[s], p, j0, zr[s]);
     }
+    load_keys(pb + 16 * S);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const float av[4] = {a[s].x, a[s].y, a[s].z, a[s].w};
@@ -514,14 +580,14 @@ k_lin_wgrad(const float* __restrict__ z, int64_t ld_z, const float* __restrict__
       }
     }
   }
-  // lane (i, g) of block (jb, nb) holds j = 16 jb + 4 g + r, c = c0 + 4 i + nb
+  // lane (i, g) of block (jb, nb) holds j = KB (4 g + r) + jb, c = c0 + 4 i + nb
   for (int w = 0; w < 4; ++w) {
     if (wave == w) {
 #pragma unroll
       for (int jb = 0; jb < KB; ++jb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          f32x4* d = reinterpret_cast<f32x4*>(&sum[(16 * jb + 4 * lg + r) * kLinCols + 4 * li]);
+          f32x4* d = reinterpret_cast<f32x4*>(&sum[(KB * (4 * lg + r) + jb) * kLinCols + 4 * li]);
           f32x4 v = f32x4{acc[jb][0][r], acc[jb][1][r], acc[jb][2][r], acc[jb][3][r]};
           if (w > 0) v += *d;
           *d = v;
@@ -534,7 +600,7 @@ k_lin_wgrad(const float* __restrict__ z, int64_t ld_z, const float* __restrict__
     float v = bs[jb];
     v += __shfl_xor(v, 16);
     v += __shfl_xor(v, 32);
-    if (lg == 0) sb[wave][16 * jb + li] = v;
+    if (lg == 0) sb[wave][j0 + jb] = v;
   }
   __syncthreads();
   float* dst = part + static_cast<int64_t>(blockIdx.x) * (static_cast<int64_t>(K) * C + K);
@@ -653,9 +719,12 @@ int64_t classify_backward_partial_floats(int64_t m, int K, int C) {
   return static_cast<int64_t>(chunks) * (static_cast<int64_t>(K) * C + K);
 }
 
-void launch_linear_backward(const float* z, int64_t ld_z, const float* W, int K, int C, int64_t m, const float* f,
-                            int64_t ld_f, float* df, int64_t ld_df, float* dW, int C_out, float* db, float* part,
-                            hipStream_t s) {
+namespace {
+// df by rows that allow 16-byte loads or not (Rows4), dW and db by Rows
+template <class Rows4, class Rows>
+void linear_backward(const Rows4& rows4, const Rows& rows, const float* W, int K, int C, int64_t m, const float* f,
+                     int64_t ld_f, float* df, int64_t ld_df, float* dW, int C_out, float* db, float* part,
+                     hipStream_t s) {
   const unsigned col_blocks = static_cast<unsigned>((C + kLinCols - 1) / kLinCols);
   const int kb = (K + 15) / 16;   // K <= 64
   auto by_kb = [&](auto go) {
@@ -666,13 +735,9 @@ void launch_linear_backward(const float* z, int64_t ld_z, const float* W, int K,
   };
   if (df && m > 0) {
     const unsigned gx = static_cast<unsigned>(std::min<int64_t>((m + 63) / 64, std::max(1u, 2048 / col_blocks)));
-    const bool v4 = K % 4 == 0 && ld_z % 4 == 0 && (reinterpret_cast<uintptr_t>(z) & 15u) == 0;
     by_kb([&](auto kb_c) {
-      constexpr int KB = decltype(kb_c)::value;
-      if (v4)
-        launch((k_lin_dinput<KB, true>), dim3(gx, col_blocks), dim3(kBlock), 0, s, z, ld_z, W, K, C, m, df, ld_df);
-      else
-        launch((k_lin_dinput<KB, false>), dim3(gx, col_blocks), dim3(kBlock), 0, s, z, ld_z, W, K, C, m, df, ld_df);
+      launch((k_lin_dinput<decltype(kb_c)::value, Rows4>), dim3(gx, col_blocks), dim3(kBlock), 0, s, rows4, W, K, C, m,
+             df, ld_df);
     });
   }
   if (!dW && !db) return;
@@ -682,12 +747,30 @@ void launch_linear_backward(const float* z, int64_t ld_z, const float* W, int K,
   lin_chunks(m, K, C, &chunk, &chunks);
   if (m > 0)
     by_kb([&](auto kb_c) {
-      constexpr int KB = decltype(kb_c)::value;
-      launch(k_lin_wgrad<KB>, dim3(static_cast<unsigned>(chunks), col_blocks), dim3(kBlock), 0, s, z, ld_z, f, ld_f,
-             K, C, m, chunk, part);
+      launch((k_lin_wgrad<decltype(kb_c)::value, Rows>), dim3(static_cast<unsigned>(chunks), col_blocks), dim3(kBlock), 0,
+             s, rows, f, ld_f, K, C, m, chunk, part);
     });
   launch(k_lin_reduce, dim3(static_cast<unsigned>((nout + kLinRedOut - 1) / kLinRedOut)), dim3(kBlock), 0, s,
          static_cast<const float*>(part), m > 0 ? chunks : 0, K, C, C_out, dW, db);
+}
+}  // namespace
+
+void launch_linear_backward(const float* z, int64_t ld_z, const float* W, int K, int C, int64_t m, const float* f,
+                            int64_t ld_f, float* df, int64_t ld_df, float* dW, int C_out, float* db, float* part,
+                            hipStream_t s) {
+  const GivenRows<true> r4{z, ld_z, K};
+  const GivenRows<false> r1{z, ld_z, K};
+  if (K % 4 == 0 && ld_z % 4 == 0 && (reinterpret_cast<uintptr_t>(z) & 15u) == 0)
+    linear_backward(r4, r4, W, K, C, m, f, ld_f, df, ld_df, dW, C_out, db, part, s);
+  else
+    linear_backward(r1, r1, W, K, C, m, f, ld_f, df, ld_df, dW, C_out, db, part, s);
+}
+
+void launch_linear_backward_routed(const int32_t* ev, const int32_t* am, const float* dX, int64_t ld_dX, const float* W,
+                                   int K, int C, int64_t m, const float* f, int64_t ld_f, float* df, int64_t ld_df,
+                                   float* dW, int C_out, float* db, float* part, hipStream_t s) {
+  const RoutedRows r{ev, am, dX, ld_dX, K};
+  linear_backward(r, r, W, K, C, m, f, ld_f, df, ld_df, dW, C_out, db, part, s);
 }
 
 void launch_classify_backward(const float* z, int64_t ld_z, const float* Wc, int K, int C, int64_t m, const float* f,

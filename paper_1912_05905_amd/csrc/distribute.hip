@@ -22,6 +22,7 @@
 // registers; each wave takes an equal range of list entries and reduces
 // the maximum across lanes.
 #include <algorithm>
+#include <type_traits>
 
 #include "lattice_internal.h"
 
@@ -167,7 +168,9 @@ __device__ inline float row_coord(float g, double sc, double m) {
 // and sums channels [c0, c0 + 8) of their rows (for each block of 8 of the
 // cin channels in turn); the workgroup adds its 256 threads by a fixed tree.
 // part[w] holds the cin sums, then the cin sums of squares.
+// EXACT: coordinates kept in fp64 (the backward's rows) instead of rounded.
 constexpr int kStatsCh = 8;
+template <bool EXACT>
 __global__ void __launch_bounds__(kBlock)
 k_dist_in_stats(const int32_t* __restrict__ entries, const int32_t* __restrict__ entry_vertex, int64_t total,
                 const float* __restrict__ pos, double sc0, double sc1, double sc2, const double4* __restrict__ mu,
@@ -187,13 +190,15 @@ k_dist_in_stats(const int32_t* __restrict__ entries, const int32_t* __restrict__
       for (int i = 0; i < kStatsCh; ++i) {
         const int c = c0 + i;
         if (c >= cin) break;
-        float x;
-        if (c == 0) x = row_coord(pos[3 * p], sc0, m.x);
-        else if (c == 1) x = row_coord(pos[3 * p + 1], sc1, m.y);
-        else if (c == 2) x = row_coord(pos[3 * p + 2], sc2, m.z);
-        else x = feat[p * ld_feat + (c - 3)];
+        double x;
+        if (c < 3) {
+          const double sc = c == 0 ? sc0 : (c == 1 ? sc1 : sc2), mc = c == 0 ? m.x : (c == 1 ? m.y : m.z);
+          x = EXACT ? static_cast<double>(pos[3 * p + c]) / sc - mc : row_coord(pos[3 * p + c], sc, mc);
+        } else {
+          x = feat[p * ld_feat + (c - 3)];
+        }
         s[i] += x;
-        ss[i] += static_cast<double>(x) * x;
+        ss[i] += x * x;
       }
     }
     double* o = part + static_cast<int64_t>(blockIdx.x) * 2 * cin;
@@ -344,13 +349,14 @@ struct LayerStats {
 #pragma unroll
       for (int r = 0; r < 4; ++r) s[nb][r] = q[nb][r] = 0.0;
   }
-  __device__ void add(const f32x4* h, bool valid) {
+  template <class V4>
+  __device__ void add(const V4* h, bool valid) {
     if (!valid) return;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const double x = h[nb][r];
+        const double x = static_cast<double>(h[nb][r]);
         s[nb][r] += x;
         q[nb][r] += x * x;
       }
@@ -748,143 +754,339 @@ void run_mlp(int stage, const MlpLds& lay, unsigned grid, hipStream_t s, const i
 
 
 // ---- Distribute + PointNet backward ----
-// The forward is recomputed in fp64 with every block's input and
-// activation kept (rows of list entries, in list order): the ReLU and the
-// maximum are discrete decisions, and fp64 takes them as exact arithmetic
-// does except within ~1e-15 of a tie.  The maximum routes dL/dx_v[c] to the
-// row of J_v holding channel c's maximum (the first in list order); each
-// block then goes backward in fp32 as a linear layer
+// The forward is recomputed in fp64 (rows of list entries, in list order): the
+// ReLU and the maximum are discrete decisions, and fp64 takes them as exact
+// arithmetic does except within ~1e-15 of a tie.  The maximum routes
+// dL/dx_v[c] to the row of J_v holding channel c's maximum (the first in list
+// order); each block then goes backward in fp32 as a linear layer
 // (launch_linear_backward, on the fp32 activations) and a GroupNorm + ReLU
 // (launch_gn_backward, whose ReLU passes where the activation is > 0).  The
 // raw rows are zero-padded to a multiple of 4 channels, each padding
 // channel a group of its own that no weight reads.
+//
+// k_dist_fwd64 is the fp64 counterpart of k_dist_mlp: STAGE 1 and 2 sum the
+// statistics of the first and second layer's outputs, STAGE 3 runs all three
+// layers, stores the blocks' normalised inputs and activations (fp32: what
+// their backward reads) and finds the maxima's rows.  Each pass recomputes the
+// layers before it from the gathered rows: at 16/32/64 channels a row is 2,700
+// multiply-adds, less time on v_mfma_f64_16x16x4_f64 than storing and reading
+// 112 doubles.  A wave owns kMlpRange list entries, 16 at a time; in the
+// product's result lane (i, g) holds row 4 r + g of the weights in register r,
+// so the weights are laid out with output 16 nb + 4 g + r there, and the
+// activations stay in registers as the next layer's operand (input 16 b + 4 g
+// + r for step (b, r)).  One thread per row and layer with every intermediate
+// in memory, and one thread per (vertex, channel) walking its list, took 906 +
+// 605 us on the 480,000 entries of a LiDAR scan, the statistics, raw rows and
+// the cleared gradient another 110; the three stages here 15 + 32 + 96 us.
 
-// Raw rows (total x cin4) in fp64: g / sigma - mu, the features, zeros.
-__global__ void __launch_bounds__(kBlock)
-k_dist_raw_rows64(const int32_t* __restrict__ entries, const int32_t* __restrict__ entry_vertex, int64_t total,
-                  const float* __restrict__ pos, double sc0, double sc1, double sc2, const double4* __restrict__ mu,
-                  const float* __restrict__ feat, int64_t ld_feat, int cf, int cin4, double* __restrict__ H64) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (e >= total) return;
-  const int64_t p = entries[e] >> 2;
-  const double4 m = mu[entry_vertex[e]];
-  double* r = H64 + e * cin4;
-  r[0] = static_cast<double>(pos[3 * p]) / sc0 - m.x;
-  r[1] = static_cast<double>(pos[3 * p + 1]) / sc1 - m.y;
-  r[2] = static_cast<double>(pos[3 * p + 2]) / sc2 - m.z;
-  for (int c = 0; c < cf; ++c) r[3 + c] = feat[p * ld_feat + c];
-  for (int c = 3 + cf; c < cin4; ++c) r[c] = 0.0;
-}
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kTile64 = 64 + 4;   // row pitch of a wave's 16 x 64 output tile (doubles)
 
-// Per-workgroup fp64 sums and sums of squares of each channel of fp64 rows
-// [w rows_per, (w + 1) rows_per): thread t takes channel t % C of rows
-// t / C, + slots, ...; the slots are added in order.  Layout as
-// launch_gn_finalize reads it.
-__global__ void __launch_bounds__(kBlock)
-k_dist_stats64(const double* __restrict__ H, int C, int64_t n, int64_t rows_per, double* __restrict__ part) {
-  __shared__ double sh[2][kBlock];
-  const int t = threadIdx.x;
-  const int slots = kBlock / C;
-  const int c = t % C, slot = t / C;
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * rows_per;
-  const int64_t r1 = min(r0 + rows_per, n);
-  double s = 0.0, ss = 0.0;
-  if (slot < slots)
-    for (int64_t v = r0 + slot; v < r1; v += slots) {
-      const double x = H[v * C + c];
-      s += x;
-      ss += x * x;
-    }
-  sh[0][t] = s;
-  sh[1][t] = ss;
-  __syncthreads();
-  if (t < C) {
-    double a = 0.0, b = 0.0;
-    for (int sl = 0; sl < slots; ++sl) {
-      a += sh[0][sl * C + t];
-      b += sh[1][sl * C + t];
-    }
-    part[static_cast<int64_t>(blockIdx.x) * 2 * C + t] = a;
-    part[static_cast<int64_t>(blockIdx.x) * 2 * C + C + t] = b;
-  }
-}
+// output that row rho of a weight fragment stands for
+__device__ inline int row64(int rho) { return 4 * (rho & 3) + (rho >> 2); }
 
-// One block forward in fp64 for every row:
-//   xhat = (h - mean_g) inv_g,  a = max(xhat gamma_c + beta_c, 0),  h' = W a + b,
-// writing xhat and a (fp32: what the backward of the block reads) and h'
-// (fp64).  W (co x ci fp32, dense) is staged in LDS as fp64 rows of kMaxC,
-// zero-padded; one thread per row.
+// One normalisation: per group mean and 1 / sqrt(var + eps), the affine
+// parameters (optional), channels and channels per group.
+struct Norm64 {
+  const double* stats;
+  const float* gamma;
+  const float* beta;
+  int C, per;
+};
+
+struct Fwd64Lds {
+  int a1, a2, a3, b, n0, n1, n2, t, end;   // in doubles; a table of a norm: means, inverses, gammas, betas
+  __host__ __device__ Fwd64Lds(int ks1, int nb1, int nb2, int nb3, int stage) {
+    a1 = 0;
+    a2 = a1 + nb1 * ks1 * 64;
+    a3 = a2 + (stage >= 2 ? nb2 * nb1 * 256 : 0);
+    b = a3 + (stage >= 3 ? nb3 * nb2 * 256 : 0);
+    n0 = b + 16 * (nb1 + nb2 + nb3);
+    n1 = n0 + 4 * 4 * ks1;
+    n2 = n1 + 4 * 16 * nb1;
+    t = n2 + 4 * 16 * nb2;
+    end = t + kWaves * (stage >= 3 ? 16 * kTile64 : 2 * kMaxC);
+  }
+  __host__ __device__ size_t bytes() const { return static_cast<size_t>(end) * 8; }
+};
+
+struct Fwd64Out {
+  double* part;             // STAGE 1, 2: per workgroup the sums, then the sums of squares
+  float *xh[3], *a[3];      // STAGE 3: the blocks' normalised inputs and activations
+  int32_t* am;              // n x c3: the row of channel c's maximum over J_v
+  double* pv;               // per range a head and a tail piece of 64 maxima
+  int32_t* pr;              // and their rows
+};
+
+template <int NB1, int NB2, int NB3, int KS, int STAGE>
 __global__ void __launch_bounds__(kBlock)
-k_dist_layer64(const double* __restrict__ Hin, int ci, const double* __restrict__ stats, int groups,
-               const float* __restrict__ gamma, const float* __restrict__ beta, const float* __restrict__ W,
-               const float* __restrict__ b, int co, int64_t rows, float* __restrict__ Xh32, float* __restrict__ A32,
-               double* __restrict__ Hout) {
-  __shared__ double sw[kMaxC * kMaxC];
-  __shared__ double sb[kMaxC], smu[kMaxC], siv[kMaxC], sg[kMaxC], sbt[kMaxC];
-  for (int i = threadIdx.x; i < co * kMaxC; i += kBlock) {
-    const int o = i / kMaxC, c = i - o * kMaxC;
-    sw[i] = c < ci ? static_cast<double>(W[o * ci + c]) : 0.0;
-  }
-  for (int i = threadIdx.x; i < co; i += kBlock) sb[i] = b ? b[i] : 0.0;
-  const int per = ci / groups;
-  for (int i = threadIdx.x; i < kMaxC; i += kBlock) {
-    const bool in = i < ci;
-    smu[i] = in ? stats[2 * (i / per)] : 0.0;
-    siv[i] = in ? stats[2 * (i / per) + 1] : 0.0;
-    sg[i] = in && gamma ? gamma[i] : 1.0;
-    sbt[i] = in && beta ? beta[i] : 0.0;
-  }
-  __syncthreads();
-  const int64_t r = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (r >= rows) return;
-  double a[kMaxC];
+k_dist_fwd64(const int32_t* __restrict__ entries, const int32_t* __restrict__ entry_vertex, int64_t total,
+             const float* __restrict__ pos, double sc0, double sc1, double sc2, const float* __restrict__ feat,
+             int64_t ld_feat, int cf, const double* __restrict__ mu, Norm64 m0, Norm64 m1, Norm64 m2,
+             const float* __restrict__ W1, const float* __restrict__ b1, const float* __restrict__ W2,
+             const float* __restrict__ b2, const float* __restrict__ W3, const float* __restrict__ b3, int ks1, int c1,
+             int c2, int c3, Fwd64Out out) {
+  extern __shared__ __align__(16) double sm64[];
+  const Fwd64Lds lay(KS, NB1, NB2, NB3, STAGE);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  const int cin = 3 + cf;
+  const int64_t range = static_cast<int64_t>(blockIdx.x) * kWaves + wave;
+  const int64_t r0 = min(range * kMlpRange, total);
+  const int64_t r1 = min(r0 + kMlpRange, total);
+  const bool active = r0 < r1;
+
+  // the wave's entries and their vertices, two per lane
+  int32_t ent[2], vtx[2];
 #pragma unroll
-  for (int i = 0; i < kMaxC; ++i) {
-    const double x = i < ci ? Hin[r * ci + i] : 0.0;
-    const double xh = (x - smu[i]) * siv[i];
-    a[i] = i < ci ? fmax(xh * sg[i] + sbt[i], 0.0) : 0.0;
-    if (i < ci) {
-      Xh32[r * ci + i] = static_cast<float>(xh);
-      A32[r * ci + i] = static_cast<float>(a[i]);
-    }
+  for (int j = 0; j < 2; ++j) {
+    const int64_t s = r0 + 64 * j + lane;
+    ent[j] = s < r1 ? entries[s] : 0;
+    vtx[j] = s < r1 ? entry_vertex[s] : -1;
   }
-  for (int o = 0; o < co; ++o) {
-    double v = sb[o];
+  const int32_t key_before = (active && r0 > 0) ? entry_vertex[r0 - 1] : -1;
+  const int32_t key_after = (active && r1 < total) ? entry_vertex[r1] : -1;
+
+  // weights in fragment order, biases, normalisation tables
+  for (int q = t; q < NB1 * KS * 64; q += kBlock) {
+    const int run = q >> 6, L = q & 63, nb = run / KS, ks = run - nb * KS;
+    const int o = 16 * nb + row64(L & 15), k = 4 * ks + (L >> 4);
+    sm64[lay.a1 + q] = (o < c1 && k < cin) ? static_cast<double>(W1[o * cin + k]) : 0.0;
+  }
+  if constexpr (STAGE >= 2)
+    for (int q = t; q < NB2 * NB1 * 256; q += kBlock) {
+      const int r = q & 3, L = (q >> 2) & 63, run = q >> 8, nb = run / NB1, kb = run - nb * NB1;
+      const int o = 16 * nb + row64(L & 15), k = 16 * kb + 4 * (L >> 4) + r;
+      sm64[lay.a2 + q] = (o < c2 && k < c1) ? static_cast<double>(W2[o * c1 + k]) : 0.0;
+    }
+  if constexpr (STAGE >= 3)
+    for (int q = t; q < NB3 * NB2 * 256; q += kBlock) {
+      const int r = q & 3, L = (q >> 2) & 63, run = q >> 8, nb = run / NB2, kb = run - nb * NB2;
+      const int o = 16 * nb + row64(L & 15), k = 16 * kb + 4 * (L >> 4) + r;
+      sm64[lay.a3 + q] = (o < c3 && k < c2) ? static_cast<double>(W3[o * c2 + k]) : 0.0;
+    }
+  for (int q = t; q < 16 * (NB1 + NB2 + NB3); q += kBlock) {
+    const int i1 = q, i2 = q - 16 * NB1, i3 = i2 - 16 * NB2;
+    float v = 0.f;
+    if (i2 < 0) v = (i1 < c1 && b1) ? b1[i1] : 0.f;
+    else if (i3 < 0) v = (i2 < c2 && b2) ? b2[i2] : 0.f;
+    else v = (i3 < c3 && b3) ? b3[i3] : 0.f;
+    sm64[lay.b + q] = static_cast<double>(v);
+  }
+  auto stage_norm = [&](const Norm64& m, int at, int width) {
+    for (int k = t; k < width; k += kBlock) {
+      const bool in = k < m.C;
+      sm64[at + k] = in ? m.stats[2 * (k / m.per)] : 0.0;
+      sm64[at + width + k] = in ? m.stats[2 * (k / m.per) + 1] : 0.0;
+      sm64[at + 2 * width + k] = in ? (m.gamma ? static_cast<double>(m.gamma[k]) : 1.0) : 0.0;
+      sm64[at + 3 * width + k] = in && m.beta ? static_cast<double>(m.beta[k]) : 0.0;
+    }
+  };
+  stage_norm(m0, lay.n0, 4 * KS);
+  if constexpr (STAGE >= 2) stage_norm(m1, lay.n1, 16 * NB1);
+  if constexpr (STAGE >= 3) stage_norm(m2, lay.n2, 16 * NB2);
+  __syncthreads();
+
+  // the raw row of entry i of a group: input 4 ks + g in lane (i, g)
+  const double scg = lg == 0 ? sc0 : (lg == 1 ? sc1 : (lg == 2 ? sc2 : 1.0));
+  struct Raw {
+    float x[KS];
+    double m;
+  };
+  auto gather = [&](int grp, Raw& w, int32_t& v) {
+    const int32_t e = __shfl(grp < 4 ? ent[0] : ent[1], 16 * (grp & 3) + li);
+    v = __shfl(grp < 4 ? vtx[0] : vtx[1], 16 * (grp & 3) + li);
+    const int64_t p = e >> 2;
+    const bool in = v >= 0;
+    w.x[0] = 0.f;
+    w.m = 0.0;
+    if (in && lg < 3) {
+      w.x[0] = pos[3 * p + lg];
+      w.m = mu[4 * static_cast<int64_t>(v) + lg];
+    } else if (in && cf > 0) {
+      w.x[0] = feat[p * ld_feat];
+    }
 #pragma unroll
-    for (int i = 0; i < kMaxC; ++i) v = fma(sw[o * kMaxC + i], a[i], v);
-    Hout[r * co + o] = v;
+    for (int ks = 1; ks < KS; ++ks) {
+      const int f = 4 * ks + lg - 3;
+      w.x[ks] = (in && f < cf) ? feat[p * ld_feat + f] : 0.f;
+    }
+  };
+  // normalised value and activation of channel k of table `at` (width w)
+  auto norm = [&](int at, int w, int k, double h, double& xh) {
+    xh = (h - sm64[at + k]) * sm64[at + w + k];
+    return fmax(xh * sm64[at + 2 * w + k] + sm64[at + 3 * w + k], 0.0);
+  };
+  LayerStats<(STAGE == 1 ? NB1 : (STAGE == 2 ? NB2 : 1))> stats;
+  double* T = sm64 + lay.t + wave * (STAGE >= 3 ? 16 * kTile64 : 2 * kMaxC);
+  int32_t ckey = -1, crow = 0;   // vertex whose maximum is open (wave-uniform), row of channel `lane`'s maximum
+  double cmax = 0.0;
+  auto emit = [&]() {
+    if (ckey < 0 || lane >= c3) return;
+    if (ckey == key_before || ckey == key_after) {
+      // a list cut by a range boundary: the piece it starts with is a tail
+      const int64_t at = (2 * range + (ckey == key_before ? 0 : 1)) * kMaxC + lane;
+      out.pv[at] = cmax;
+      out.pr[at] = crow;
+    } else {
+      out.am[static_cast<int64_t>(ckey) * c3 + lane] = crow;
+    }
+  };
+
+  const int groups = static_cast<int>((r1 - r0 + 15) / 16);
+  Raw w, wn;
+  int32_t v = -1, vn = -1;
+  if (groups > 0) gather(0, w, v);
+  for (int grp = 0; grp < groups; ++grp) {
+    if (grp + 1 < groups) gather(grp + 1, wn, vn);   // the next group's rows arrive during this one
+    const int64_t row = r0 + 16 * grp + li;
+    const bool live = v >= 0;
+    f64x4 h1[NB1], h2[NB2], o3[NB3];
+#pragma unroll
+    for (int nb = 0; nb < NB1; ++nb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h1[nb][r] = sm64[lay.b + 16 * nb + 4 * lg + r];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const double h = ks == 0 ? static_cast<double>(w.x[0]) / scg - w.m : static_cast<double>(w.x[ks]);
+      double xh;
+      const double a = norm(lay.n0, 4 * KS, 4 * ks + lg, h, xh);
+      if constexpr (STAGE == 3)
+        if (live && ks < ks1) {
+          out.xh[0][row * 4 * ks1 + 4 * ks + lg] = static_cast<float>(xh);
+          out.a[0][row * 4 * ks1 + 4 * ks + lg] = static_cast<float>(a);
+        }
+#pragma unroll
+      for (int nb = 0; nb < NB1; ++nb)
+        h1[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(sm64[lay.a1 + (nb * KS + ks) * 64 + lane], a, h1[nb], 0, 0, 0);
+    }
+    if constexpr (STAGE == 1) stats.add(h1, live);
+    // a block's activations from its input h, stored as float4 per 16 channels
+    auto block = [&](const auto& h, int nbi, int at, int width, int C, float* xo, float* ao, auto&& use) {
+#pragma unroll
+      for (int kb = 0; kb < nbi; ++kb) {
+        double a[4];
+        float4 fx, fa;
+        float *px = &fx.x, *pa = &fa.x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double xh;
+          a[r] = norm(at, width, 16 * kb + 4 * lg + r, h[kb][r], xh);
+          px[r] = static_cast<float>(xh);
+          pa[r] = static_cast<float>(a[r]);
+        }
+        if constexpr (STAGE == 3)
+          if (live && 16 * kb < C) {
+            *reinterpret_cast<float4*>(xo + row * C + 16 * kb + 4 * lg) = fx;
+            *reinterpret_cast<float4*>(ao + row * C + 16 * kb + 4 * lg) = fa;
+          }
+        use(kb, a);
+      }
+    };
+    if constexpr (STAGE >= 2) {
+#pragma unroll
+      for (int nb = 0; nb < NB2; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h2[nb][r] = sm64[lay.b + 16 * (NB1 + nb) + 4 * lg + r];
+      block(h1, NB1, lay.n1, 16 * NB1, c1, out.xh[1], out.a[1], [&](int kb, const double (&a)[4]) {
+#pragma unroll
+        for (int nb = 0; nb < NB2; ++nb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            h2[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(sm64[lay.a2 + ((nb * NB1 + kb) * 64 + lane) * 4 + r], a[r],
+                                                          h2[nb], 0, 0, 0);
+      });
+      if constexpr (STAGE == 2) stats.add(h2, live);
+    }
+    if constexpr (STAGE >= 3) {
+#pragma unroll
+      for (int nb = 0; nb < NB3; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o3[nb][r] = sm64[lay.b + 16 * (NB1 + NB2 + nb) + 4 * lg + r];
+      block(h2, NB2, lay.n2, 16 * NB2, c2, out.xh[2], out.a[2], [&](int kb, const double (&a)[4]) {
+#pragma unroll
+        for (int nb = 0; nb < NB3; ++nb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            o3[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(sm64[lay.a3 + ((nb * NB2 + kb) * 64 + lane) * 4 + r], a[r],
+                                                          o3[nb], 0, 0, 0);
+      });
+      // the 16 x 64 outputs go through LDS; lane c walks channel c down the
+      // rows, as in k_dist_mlp
+#pragma unroll
+      for (int nb = 0; nb < NB3; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T[li * kTile64 + 16 * nb + 4 * lg + r] = o3[nb][r];
+      const int32_t up = __shfl(v, (li + 15) & 15);
+      const uint32_t starts = static_cast<uint32_t>(__ballot(v != (li > 0 ? up : ckey))) & 0xffffu;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 4
+      for (int i = 0; i < 16; ++i) {
+        const double x = T[i * kTile64 + lane];
+        const int32_t at = static_cast<int32_t>(r0) + 16 * grp + i;
+        if ((starts >> i) & 1u) {
+          emit();
+          ckey = __builtin_amdgcn_readlane(v, i);
+          cmax = x;
+          crow = at;
+        } else if (x > cmax) {
+          cmax = x;
+          crow = at;
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the walk's reads come before the next tile's writes
+    }
+    w = wn;
+    v = vn;
+  }
+  if constexpr (STAGE == 3) {
+    emit();
+  } else {
+    // the workgroup's partial: the waves' columns added in wave order
+    stats.to_lds(T, lane);
+    __syncthreads();
+    const int cst = STAGE == 1 ? c1 : c2;
+    if (t < cst) {
+      double a = 0.0, b = 0.0;
+#pragma unroll
+      for (int q = 0; q < kWaves; ++q) {
+        a += sm64[lay.t + q * 2 * kMaxC + t];
+        b += sm64[lay.t + q * 2 * kMaxC + kMaxC + t];
+      }
+      double* o = out.part + static_cast<int64_t>(blockIdx.x) * 2 * cst;
+      o[t] = a;
+      o[cst + t] = b;
+    }
   }
 }
 
-// The maximum's gradient: thread (v, c) finds the first row of J_v holding
-// channel c's maximum (fp64 rows) and writes dX[v][c] there (dH3 is zero
-// elsewhere).
+// Lists cut by range boundaries: the range a list starts in takes its tail
+// piece and the head pieces of the following ranges, the first maximum in list
+// order; lane c holds channel c, a wave a range.
 __global__ void __launch_bounds__(kBlock)
-k_dist_route_max(const int32_t* __restrict__ offsets, int64_t n, const double* __restrict__ H3, int C3,
-                 const float* __restrict__ dX, int64_t ld_dX, float* __restrict__ dH3) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (i >= n * C3) return;
-  const int64_t v = i / C3;
-  const int c = static_cast<int>(i - v * C3);
-  const int64_t b = offsets[v], e = offsets[v + 1];
-  if (b >= e) return;
-  int64_t best = b;
-  double top = H3[b * C3 + c];
-  for (int64_t r = b + 1; r < e; ++r) {
-    const double x = H3[r * C3 + c];
+k_dist_route_finish(const int32_t* __restrict__ offsets, const int32_t* __restrict__ entry_vertex, int64_t total,
+                    int c3, const double* __restrict__ pv, const int32_t* __restrict__ pr, int32_t* __restrict__ am) {
+  const int lane = threadIdx.x & 63;
+  const int64_t range = static_cast<int64_t>(blockIdx.x) * kWaves + (threadIdx.x >> 6);
+  const int64_t r1 = (range + 1) * kMlpRange;
+  if (r1 >= total || lane >= c3) return;
+  const int32_t v = entry_vertex[r1];
+  const int64_t vb = offsets[v], ve = offsets[v + 1];
+  if (vb < range * kMlpRange || vb >= r1) return;   // starts at r1, or in an earlier range
+  const int64_t last = (ve - 1) / kMlpRange;
+  double top = pv[(2 * range + 1) * kMaxC + lane];
+  int32_t best = pr[(2 * range + 1) * kMaxC + lane];
+#pragma unroll 4
+  for (int64_t q = range + 1; q <= last; ++q) {
+    const double x = pv[2 * q * kMaxC + lane];
+    const int32_t b = pr[2 * q * kMaxC + lane];
     if (x > top) {
       top = x;
-      best = r;
+      best = b;
     }
   }
-  dH3[best * C3 + c] = dX[v * ld_dX + c];
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_dist_zero(float* __restrict__ x, int64_t count) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < count;
-       i += static_cast<int64_t>(gridDim.x) * kBlock)
-    x[i] = 0.f;
+  am[static_cast<int64_t>(v) * c3 + lane] = best;
 }
 
 // List position of every reference: at[entries[s]] = s.
@@ -909,11 +1111,12 @@ k_dist_dfeat(const int32_t* __restrict__ at, int64_t m, const float* __restrict_
 }
 
 // Zero-padded copies of the first layer's weights (C1 x cin -> C1 x cin4)
-// and of the raw rows' gamma / beta (padding: 1 / 0).
+// and of the raw rows' gamma / beta (padding: 1 / 0), and the padding groups'
+// statistics (0: their rows are 0).
 __global__ void __launch_bounds__(kBlock)
 k_dist_pad_params(const float* __restrict__ W1, int C1, int cin, int cin4, const float* __restrict__ gamma,
                   const float* __restrict__ beta, float* __restrict__ W1p, float* __restrict__ gp,
-                  float* __restrict__ bp) {
+                  float* __restrict__ bp, double* __restrict__ stats) {
   for (int i = threadIdx.x; i < C1 * cin4; i += kBlock) {
     const int o = i / cin4, c = i - o * cin4;
     W1p[i] = c < cin ? W1[o * cin + c] : 0.f;
@@ -921,16 +1124,49 @@ k_dist_pad_params(const float* __restrict__ W1, int C1, int cin, int cin4, const
   for (int c = threadIdx.x; c < cin4; c += kBlock) {
     gp[c] = c < cin && gamma ? gamma[c] : 1.f;
     bp[c] = c < cin && beta ? beta[c] : 0.f;
+    if (c >= cin) stats[2 * c] = stats[2 * c + 1] = 0.0;
   }
 }
 
-// rows per workgroup of k_dist_stats64 and the number of workgroups
-void stats64_parts(int64_t n, int C, int64_t* nparts, int64_t* rows_per) {
-  const int slots = kBlock / C;
-  int64_t rp = std::max<int64_t>(slots, (n + kStatsMaxParts - 1) / kStatsMaxParts);
-  rp = (rp + slots - 1) / slots * slots;
-  *rows_per = rp;
-  *nparts = std::max<int64_t>(1, (n + rp - 1) / rp);
+template <int NB1, int NB2, int NB3, int KS>
+void run_fwd64_as(int stage, unsigned grid, hipStream_t s, const int32_t* entries, const int32_t* ev, int64_t total,
+                  const float* pos, const double sc[3], const float* feat, int64_t ld_feat, int cf, const double* mu,
+                  const Norm64 (&nm)[3], const float* W1, const float* b1, const float* W2, const float* b2,
+                  const float* W3, const float* b3, int ks1, int C1, int C2, int C3, const Fwd64Out& out) {
+  auto k1 = k_dist_fwd64<NB1, NB2, NB3, KS, 1>;
+  auto k2 = k_dist_fwd64<NB1, NB2, NB3, KS, 2>;
+  auto k3 = k_dist_fwd64<NB1, NB2, NB3, KS, 3>;
+  auto kernel = stage == 1 ? k1 : (stage == 2 ? k2 : k3);
+  const Fwd64Lds lay(KS, NB1, NB2, NB3, stage);
+  static bool lds_limit_set[3] = {false, false, false};
+  if (!lds_limit_set[stage - 1]) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              static_cast<int>(lay.bytes()));
+    lds_limit_set[stage - 1] = true;
+  }
+  launch(kernel, dim3(grid), dim3(kBlock), static_cast<uint32_t>(lay.bytes()), s, entries, ev, total, pos, sc[0], sc[1],
+         sc[2], feat, ld_feat, cf, mu, nm[0], nm[1], nm[2], W1, b1, W2, b2, W3, b3, ks1, C1, C2, C3, out);
+}
+
+// The paper's 16-32-64 block with up to 5 raw features has its own instance;
+// layers of at most 32 channels before the last run padded to 32-32-64, every
+// other shape to 64-64-64.
+void run_fwd64(int stage, unsigned grid, hipStream_t s, const int32_t* entries, const int32_t* ev, int64_t total,
+               const float* pos, const double sc[3], const float* feat, int64_t ld_feat, int cf, const double* mu,
+               const Norm64 (&nm)[3], const float* W1, const float* b1, const float* W2, const float* b2,
+               const float* W3, const float* b3, int ks1, int C1, int C2, int C3, const Fwd64Out& out) {
+  auto as = [&](auto nb1, auto nb2, auto ks) {
+    run_fwd64_as<decltype(nb1)::value, decltype(nb2)::value, 4, decltype(ks)::value>(
+        stage, grid, s, entries, ev, total, pos, sc, feat, ld_feat, cf, mu, nm, W1, b1, W2, b2, W3, b3, ks1, C1, C2, C3,
+        out);
+  };
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  using Four = std::integral_constant<int, 4>;
+  using Eight = std::integral_constant<int, 8>;
+  if (C1 <= 16 && C2 <= 32 && ks1 <= 2) as(One{}, Two{}, Two{});
+  else if (C1 <= 32 && C2 <= 32) as(Two{}, Two{}, Eight{});
+  else as(Four{}, Four{}, Eight{});
 }
 
 inline unsigned grid_rows(int64_t rows) {
@@ -989,7 +1225,7 @@ void launch_distribute(const int32_t* offsets, const int32_t* entries, const int
   // the raw rows' statistics -> table 0
   const int cin = 3 + cf;
   const int64_t np0 = std::min<int64_t>(kStatsMaxParts, (total + kBlock - 1) / kBlock);
-  launch(k_dist_in_stats, dim3(static_cast<unsigned>(np0)), dim3(kBlock), 0, s, entries,
+  launch(k_dist_in_stats<false>, dim3(static_cast<unsigned>(np0)), dim3(kBlock), 0, s, entries,
          static_cast<const int32_t*>(ev), total, pos, scale[0], scale[1], scale[2], static_cast<const double4*>(mu4),
          feat, ld_feat, cin, part);
   auto groups = [](int C) { return C <= 32 ? C : 32; };
@@ -1026,23 +1262,31 @@ void launch_distribute(const int32_t* offsets, const int32_t* entries, const int
 namespace lat {
 
 // Work space of the backward, carved in this order (each piece 256-byte
-// aligned): means, mean partials, entry vertices, list positions, two fp64
-// row buffers, the blocks' normalised inputs and activations (fp32), dH3, two gradient
-// buffers, padded parameters, normalisation tables, stats, coefficients,
-// statistics partials, linear-layer partials.
+// aligned): means, mean partials, entry vertices, list positions, the blocks'
+// normalised inputs and activations (fp32), the maxima's rows and the pieces of
+// cut lists, two gradient buffers, padded parameters, normalisation tables,
+// stats, coefficients, statistics partials, linear-layer partials.
+namespace {
+// statistics partials: of the raw rows, of a layer's outputs (one per
+// workgroup of k_dist_fwd64), of the GroupNorm backward
+int64_t backward_stats_bytes(int64_t total, int64_t widest) {
+  return std::max<int64_t>(gn_workspace_bytes(total, static_cast<int>(widest)),
+                           std::max<int64_t>(kStatsMaxParts, mlp_grid(total)) * 2 * widest * 8);
+}
+}  // namespace
+
 int64_t distribute_backward_workspace_bytes(int64_t n, int64_t m, int64_t total, int cf, int C1, int C2, int C3) {
   auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
   const int cin4 = (3 + cf + 3) / 4 * 4;
   const int64_t mean_spans = (total + kMeanSpan - 1) / kMeanSpan;
   const int64_t widest = std::max<int64_t>(std::max(cin4, C1), std::max(C2, C3));
+  const int64_t pieces = 2 * kWaves * mlp_grid(total) * kMaxC;
   int64_t b = up(32 * n) + up(2 * mean_spans * 32) + up(4 * total) + up(4 * std::max<int64_t>(4 * m, 1));
-  b += 2 * up(8 * total * widest);
   b += 2 * (up(4 * total * cin4) + up(4 * total * C1) + up(4 * total * C2));
-  b += up(4 * total * C3) + 2 * up(4 * total * widest);
+  b += up(4 * n * C3) + up(8 * pieces) + up(4 * pieces) + 2 * up(4 * total * widest);
   b += up(4 * (C1 * cin4 + 2 * cin4 + 2 * cin4));
   b += 3 * up(4 * 2 * widest) + 3 * up(8 * 2 * widest) + up(4 * 4 * widest);
-  // k_dist_stats64 runs at most kStatsMaxParts workgroups
-  b += up(std::max<int64_t>(gn_workspace_bytes(total, static_cast<int>(widest)), kStatsMaxParts * 2 * widest * 8));
+  b += up(backward_stats_bytes(total, widest));
   int64_t lin = 0;
   const int ks[3] = {C1, C2, C3}, cs[3] = {cin4, C1, C2};
   for (int i = 0; i < 3; ++i) lin = std::max(lin, classify_backward_partial_floats(total, ks[i], cs[i]));
@@ -1073,14 +1317,15 @@ void launch_distribute_backward(const int32_t* offsets, const int32_t* entries, 
   double4* mt = mh + mean_spans;
   int32_t* ev = reinterpret_cast<int32_t*>(take(4 * total));
   int32_t* at = reinterpret_cast<int32_t*>(take(4 * std::max<int64_t>(4 * m, 1)));
-  double* h64[2] = {reinterpret_cast<double*>(take(8 * total * widest)),
-                    reinterpret_cast<double*>(take(8 * total * widest))};
   const int ci[3] = {cin4, C1, C2}, co[3] = {C1, C2, C3};
   float* Xh32[3];   // each block's normalised input
   float* A32[3];    // and its activation
   for (int i = 0; i < 3; ++i) Xh32[i] = reinterpret_cast<float*>(take(4 * total * ci[i]));
   for (int i = 0; i < 3; ++i) A32[i] = reinterpret_cast<float*>(take(4 * total * ci[i]));
-  float* dH3 = reinterpret_cast<float*>(take(4 * total * C3));
+  const int64_t pieces = 2 * kWaves * mlp_grid(total) * kMaxC;
+  int32_t* am = reinterpret_cast<int32_t*>(take(4 * n * C3));
+  double* pv = reinterpret_cast<double*>(take(8 * pieces));
+  int32_t* pr = reinterpret_cast<int32_t*>(take(4 * pieces));
   float* gA = reinterpret_cast<float*>(take(4 * total * widest));
   float* gB = reinterpret_cast<float*>(take(4 * total * widest));
   float* W1p = reinterpret_cast<float*>(take(4 * (C1 * cin4 + 2 * cin4 + 2 * cin4)));
@@ -1093,14 +1338,13 @@ void launch_distribute_backward(const int32_t* offsets, const int32_t* entries, 
   for (int i = 0; i < 3; ++i) pre[i] = reinterpret_cast<float*>(take(4 * 2 * widest));
   for (int i = 0; i < 3; ++i) stats[i] = reinterpret_cast<double*>(take(8 * 2 * widest));
   float* coef = reinterpret_cast<float*>(take(4 * 4 * widest));
-  void* gnw = take(std::max<int64_t>(gn_workspace_bytes(total, static_cast<int>(widest)), kStatsMaxParts * 2 * widest * 8));
+  void* gnw = take(backward_stats_bytes(total, widest));
   float* part = reinterpret_cast<float*>(w);
 
   auto groups = [](int C) { return C <= 32 ? C : 32; };
   const float* gam[3] = {g0p, gamma ? gamma + cin : nullptr, gamma ? gamma + cin + C1 : nullptr};
   const float* bet[3] = {b0p, beta ? beta + cin : nullptr, beta ? beta + cin + C1 : nullptr};
   const float* Ws[3] = {W1p, W2, W3};
-  const float* bs[3] = {b1, b2, b3};
   float* dWs[3] = {dW1, dW2, dW3};
   float* dbs[3] = {db1, db2, db3};
   const int wout[3] = {cin, C1, C2};
@@ -1108,7 +1352,8 @@ void launch_distribute_backward(const int32_t* offsets, const int32_t* entries, 
   float* dbet[3] = {db0, dbeta ? dbeta + cin : nullptr, dbeta ? dbeta + cin + C1 : nullptr};
 
   // forward in fp64, keeping every block's input and activation
-  launch(k_dist_pad_params, dim3(1), dim3(kBlock), 0, s, W1, C1, cin, cin4, gamma, beta, W1p, g0p, b0p);
+  launch(k_dist_pad_params, dim3(1), dim3(kBlock), 0, s, W1, C1, cin, cin4, gamma, beta, W1p, g0p, b0p, stats[0]);
+  double* gpart = static_cast<double*>(gnw);
   if (total > 0) {
     launch(k_dist_mean, dim3(static_cast<unsigned>(mean_spans)), dim3(kBlock), 0, s, offsets, entries, chunk_first,
            chunk, n, total, pos, scale[0], scale[1], scale[2], mu4, mh, mt, ev, INT64_MAX, static_cast<float*>(nullptr),
@@ -1117,34 +1362,44 @@ void launch_distribute_backward(const int32_t* offsets, const int32_t* entries, 
       launch(k_dist_mean_finish, dim3(static_cast<unsigned>((mean_spans + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
              offsets, chunk_first, chunk, mean_spans, mu4, static_cast<const double4*>(mh),
              static_cast<const double4*>(mt));
-    launch(k_dist_raw_rows64, dim3(grid_rows(total)), dim3(kBlock), 0, s, entries, static_cast<const int32_t*>(ev),
-           total, pos, scale[0], scale[1], scale[2], static_cast<const double4*>(mu4), feat, ld_feat, cf, cin4, h64[0]);
   }
-  for (int i = 0; i < 3; ++i) {
-    int64_t np, rp;
-    stats64_parts(total, ci[i], &np, &rp);
-    double* gpart = static_cast<double*>(gnw);
+  const int64_t np0 = std::max<int64_t>(1, std::min<int64_t>(kStatsMaxParts, (total + kBlock - 1) / kBlock));
+  if (total > 0)
+    launch(k_dist_in_stats<true>, dim3(static_cast<unsigned>(np0)), dim3(kBlock), 0, s, entries,
+           static_cast<const int32_t*>(ev), total, pos, scale[0], scale[1], scale[2], static_cast<const double4*>(mu4),
+           feat, ld_feat, cin, gpart);
+  launch_gn_finalize(gpart, np0, cin, cin, total, gamma, beta, eps, pre[0], s, stats[0]);
+  const Norm64 nm[3] = {{stats[0], gamma, beta, cin, 1},
+                        {stats[1], gam[1], bet[1], C1, C1 / groups(C1)},
+                        {stats[2], gam[2], bet[2], C2, C2 / groups(C2)}};
+  const Fwd64Out fo{gpart, {Xh32[0], Xh32[1], Xh32[2]}, {A32[0], A32[1], A32[2]}, am, pv, pr};
+  for (int stage = 1; stage <= 3; ++stage) {
     if (total > 0)
-      launch(k_dist_stats64, dim3(static_cast<unsigned>(np)), dim3(kBlock), 0, s, static_cast<const double*>(h64[i & 1]),
-             ci[i], total, rp, gpart);
-    launch_gn_finalize(gpart, np, ci[i], groups(ci[i]), total, gam[i], bet[i], eps, pre[i], s, stats[i]);
-    if (total > 0)
-      launch(k_dist_layer64, dim3(grid_rows(total)), dim3(kBlock), 0, s, static_cast<const double*>(h64[i & 1]), ci[i],
-             static_cast<const double*>(stats[i]), groups(ci[i]), gam[i], bet[i], Ws[i], bs[i], co[i], total, Xh32[i],
-             A32[i], h64[(i + 1) & 1]);
+      run_fwd64(stage, static_cast<unsigned>(mlp_grid(total)), s, entries, static_cast<const int32_t*>(ev), total, pos,
+                scale, feat, ld_feat, cf, reinterpret_cast<const double*>(mu4), nm, W1, b1, W2, b2, W3, b3, cin4 / 4, C1,
+                C2, C3, fo);
+    if (stage < 3) {
+      const int C = stage == 1 ? C1 : C2;
+      launch_gn_finalize(gpart, mlp_grid(total), C, groups(C), total, gam[stage], bet[stage], eps, pre[stage], s,
+                         stats[stage]);
+    }
   }
-  // the maximum, then the three blocks backward in fp32
-  const unsigned zg = static_cast<unsigned>(std::min<int64_t>(8192, (total * C3 + kBlock - 1) / kBlock + 1));
-  launch(k_dist_zero, dim3(zg), dim3(kBlock), 0, s, dH3, total * C3);
-  if (n > 0)
-    launch(k_dist_route_max, dim3(grid_rows(n * C3)), dim3(kBlock), 0, s, offsets, n,
-           static_cast<const double*>(h64[1]), C3, dX, ld_dX, dH3);
-  const float* g = dH3;
+  if (total > kMlpRange)
+    launch(k_dist_route_finish, dim3(static_cast<unsigned>(mlp_grid(total))), dim3(kBlock), 0, s, offsets,
+           static_cast<const int32_t*>(ev), total, C3, static_cast<const double*>(pv), static_cast<const int32_t*>(pr),
+           am);
+  // the three blocks backward in fp32; the last one's rows are dX routed to
+  // the maxima's rows
+  const float* g = nullptr;
   for (int i = 2; i >= 0; --i) {
     // dA = g W_i, dW_i, db_i on the activations; then dH_i = GroupNorm +
     // ReLU backward of dA
-    launch_linear_backward(g, co[i], Ws[i], co[i], ci[i], total, A32[i], ci[i], gA, ci[i], dWs[i], wout[i],
-                           dbs[i], part, s);
+    if (i == 2)
+      launch_linear_backward_routed(ev, am, dX, ld_dX, Ws[i], co[i], ci[i], total, A32[i], ci[i], gA, ci[i], dWs[i],
+                                    wout[i], dbs[i], part, s);
+    else
+      launch_linear_backward(g, co[i], Ws[i], co[i], ci[i], total, A32[i], ci[i], gA, ci[i], dWs[i], wout[i], dbs[i],
+                             part, s);
     launch_gn_backward(Xh32[i], ci[i], gA, ci[i], ci[i], groups(ci[i]), total, gam[i], nullptr, stats[i], dgam[i],
                        dbet[i], coef, gB, ci[i], gnw, s, A32[i], ci[i], true);
     g = gB;   // read by the next block's linear backward, which writes gA again

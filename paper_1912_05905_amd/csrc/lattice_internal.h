@@ -328,6 +328,12 @@ int64_t classify_backward_partial_floats(int64_t m, int K, int C);
 void launch_linear_backward(const float* z, int64_t ld_z, const float* W, int K, int C, int64_t m, const float* f,
                             int64_t ld_f, float* df, int64_t ld_df, float* dW, int C_out, float* db, float* part,
                             hipStream_t s);
+// likewise for rows z_p[j] = dX[ev[p]][j] where am[ev[p]][j] = p, else 0 (am: K
+// row indices per vertex, 16-byte aligned; K a multiple of 4; dX 16-byte
+// aligned, ld_dX a multiple of 4)
+void launch_linear_backward_routed(const int32_t* ev, const int32_t* am, const float* dX, int64_t ld_dX, const float* W,
+                                   int K, int C, int64_t m, const float* f, int64_t ld_f, float* df, int64_t ld_df,
+                                   float* dW, int C_out, float* db, float* part, hipStream_t s);
 void launch_classify_backward(const float* z, int64_t ld_z, const float* Wc, int K, int C, int64_t m, const float* f,
                               float* df, float* dWc, float* dbc, float* part, hipStream_t s);
 // a = max(x pre[c] + pre[C + c], 0) for fp32 x (n x C), the pre-activated

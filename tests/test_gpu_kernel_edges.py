@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from tests import parity as P
-from tests.test_gpu_parity import L, O, _cloud, _dev, _host, _pair  # noqa: F401
+from tests.test_gpu_parity import L, O, _cloud, _dev, _distribute_backward_case, _host, _pair  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +53,16 @@ def test_weight_gradient_tiles(L, O, m, cin, cout, dtype):  # noqa: F811
         _, none, gdb = fn(gs, dev(X[ps]), None, dev(dY[pd]), want_dx=False, want_dw=False)
         assert none is None
         P.assert_close(_host(gdb), odb, P.TOL_F32, f"dbias alone m={m} {cin}->{cout} {dtype}")
+
+
+# Distribute + PointNet backward: 16-row groups, 128-entry ranges cut inside and between lists, every weight instance
+@pytest.mark.parametrize("m,cf,widths,clump", [(4, 5, (16, 32, 64), 0), (32, 1, (16, 16, 16), 0), (33, 6, (16, 32, 64), 0),
+                                               (600, 2, (32, 16, 48), 400), (700, 13, (32, 32, 64), 3),
+                                               (500, 0, (64, 32, 32), 200)])
+def test_distribute_backward_tiles(L, O, m, cf, widths, clump):  # noqa: F811
+    rng = np.random.default_rng(m)
+    pos = _cloud(2200 + m, m, 0.6)
+    pos[m // 3:m // 3 + clump] = pos[0] + 1e-4 * rng.random((clump, 3)).astype(np.float32)
+    F = rng.normal(size=(m, cf)).astype(np.float32) if cf else None
+    gl, ol, g2o = _pair(L, O, pos, 0.1)
+    _distribute_backward_case(L, O, gl, ol, g2o, pos, F, widths, m)
