@@ -195,16 +195,26 @@ void conv_launch(const int32_t* nbr, int64_t ldn, int64_t n_out, const void* in,
 // ---------------------------------------------------------------------------
 // LDS-staged pipeline.  A stage is one tap and KC channels.  The whole
 // workgroup gathers the stage's A tile (BM neighbour rows, KC channels) and
-// B tile (BN weight rows, KC channels) into LDS with 16-byte loads, 8 or 16
-// lanes per row segment; the next stage's global loads are issued before the
-// current stage is multiplied, so their latency hides behind the MFMAs.  The
-// 16-byte chunks of an LDS row are stored in an order permuted by the row
-// (chunk c of row r at c ^ swz(r)), so that the 16 rows an MFMA fragment
-// reads, and the chunks a copy writes, fall in different banks: measured on
-// gfx950 with rocprofv3 (SQ_LDS_BANK_CONFLICT), rows padded by 16 bytes cost
-// about 3 conflict cycles per ds_read_b128, these permutations none.
+// B tile (BN weight rows, KC channels) into LDS with 16-byte loads, 4 to 16
+// lanes per row segment.  The 16-byte chunks of an LDS row are stored in an
+// order permuted by the row (chunk c of row r at c ^ swz(r)), so that the 16
+// rows an MFMA fragment reads, and the chunks a copy writes, fall in different
+// banks: measured on gfx950 with rocprofv3 (SQ_LDS_BANK_CONFLICT), rows padded
+// by 16 bytes cost about 3 conflict cycles per ds_read_b128, these
+// permutations none.
 // Workgroups are numbered so that each XCD gets a contiguous range of row
 // tiles: neighbouring rows (the gather's halo) then stay in that XCD's L2.
+//
+// What bounds it is how early a stage's loads are issued: left to itself the
+// compiler sinks them to the end of the step, right before the barrier that
+// precedes their copy to LDS.  Scheduling groups therefore order the step (see
+// there).  To issue the loads early they have to be cheap and free of
+// branches: the table of a tile holds byte offsets, a load's address is that
+// offset plus a scalar, and the tap and channel are stepped rather than divided
+// out of the stage number.  With the loads sunk (and a wait for every load in
+// flight in front of each) the fp32 convolutions of a LiDAR scan's network took
+// 950 us, and 760 us here; a layer 128->128 on 6.4k vertices 30 and 26 us; bf16
+// 256->256 on 239k vertices 513 and 420 us.
 // ---------------------------------------------------------------------------
 template <bool BF16, int BM, int BN, int WM, int WN, int KCB>
 struct LdsConv {
@@ -220,15 +230,15 @@ struct LdsConv {
   static constexpr int RM = BM / (16 * WM);
   static constexpr int RN = BN / (16 * WN);
   static constexpr int KS = BF16 ? 32 : 16;         // channels per MFMA step
-  static constexpr int EPL = BF16 ? 8 : 4;          // elements per lane per MFMA step
   static constexpr int A_PER_T = BM * CPR / kBlock; // A chunks copied per thread
-  static constexpr int B_PER_T = (BN * CPR + kBlock - 1) / kBlock;
+  static constexpr int B_PER_T = BN * CPR / kBlock;
   static constexpr int A_BYTES = BM * LDR * U;
   static constexpr int B_BYTES = BN * LDR * U;
-  static constexpr int LDS_BYTES = 2 * (A_BYTES + B_BYTES) + kTaps * BM * 4 + 32 * 4;
+  static constexpr int LDS_BYTES = 2 * (A_BYTES + B_BYTES) + kTaps * BM * 4 + 16;
   static_assert(WM * WN == kWaves, "four waves");
   static_assert(RM >= 1 && RN >= 1, "wave tile");
-  static_assert(A_PER_T >= 1 && BM * CPR % kBlock == 0, "A copy split");
+  static_assert(BM * CPR % kBlock == 0 && BN * CPR % kBlock == 0, "copy split");
+  static_assert(kBlock % BM == 0 || BM % kBlock == 0, "table rows per thread");
   static_assert(CPR == 4 || CPR == 8 || CPR == 16, "chunk permutation");
   static_assert(KC % KS == 0 && KS * U == 64, "an MFMA step reads 4 chunks of a row");
 };
@@ -237,21 +247,24 @@ struct LdsConv {
 // per-channel scale and shift, then a ReLU) is applied to every gathered
 // input value of a neighbour that exists, as the stage is copied to LDS;
 // pre holds Cin scales then Cin shifts.
-template <bool BF16, int BM, int BN, int WM, int WN, int KCB, int NS, bool BUF, int SCHED, bool PRE>
+// BUF: loads through buffer resources; else (operands beyond their reach)
+// plain loads from valid addresses, replaced by zeros.
+template <bool BF16, int BM, int BN, int WM, int WN, int KCB, int NS, bool BUF, bool PRE>
 __global__ void __launch_bounds__(kBlock)
 k_conv_lds(const int32_t* __restrict__ nbr, int64_t ldn, int64_t n_out, const void* __restrict__ in,
            int64_t ld_in, int Cin, const void* __restrict__ W, const float* __restrict__ bias, int Cout,
            int relu, void* __restrict__ out, int64_t ld_out, const int32_t* __restrict__ rows,
-           unsigned row_tiles, int splits, float* __restrict__ part, uint32_t in_bytes, uint32_t w_bytes,
-           const float* __restrict__ pre, const void* __restrict__ res, int64_t ld_res) {
+           unsigned row_tiles, uint32_t in_bytes, uint32_t w_bytes, const float* __restrict__ pre,
+           const void* __restrict__ res, int64_t ld_res) {
   using P = LdsConv<BF16, BM, BN, WM, WN, KCB>;
   using E = typename std::conditional<BF16, uint16_t, float>::type;
   extern __shared__ __align__(16) unsigned char smem[];
   E* As = reinterpret_cast<E*>(smem);
   E* Bs = reinterpret_cast<E*>(smem + 2 * P::A_BYTES);
+  // [tap][row]: byte offset of the neighbour's input row (BUF; kOutOfRange when
+  // missing) or its number (-1 when missing)
   int32_t* nbt = reinterpret_cast<int32_t*>(smem + 2 * (P::A_BYTES + P::B_BYTES));
-  int32_t* tflag = nbt + kTaps * BM;  // [16] tap used by some row of the tile
-  int32_t* tlist = tflag + 16;        // [16] bf16: used taps, count in tlist[15]
+  uint32_t* used_s = reinterpret_cast<uint32_t*>(nbt + kTaps * BM);
   float* pre_s = reinterpret_cast<float*>(smem + P::LDS_BYTES);   // PRE: [Cin] scales, [Cin] shifts
 
   const int tid = threadIdx.x;
@@ -274,204 +287,215 @@ k_conv_lds(const int32_t* __restrict__ nbr, int64_t ldn, int64_t n_out, const vo
   const int col0 = static_cast<int>(item - tile * col_tiles) * BN;
   const int wm = wave % WM, wn = wave / WM;
 
-  // split z of the K dimension takes taps [tb, te)
-  const int tb = static_cast<int>(blockIdx.z) * kTaps / splits;
-  const int te = (static_cast<int>(blockIdx.z) + 1) * kTaps / splits;
-  // Taps that no row of the tile uses are skipped: their A rows are all
-  // zero.  Rows are multiplied independently, so the result of a row does
-  // not depend on which other rows share its tile.
-  if (tid < 16) tflag[tid] = 0;
+  // The tile's neighbours.  Taps that no row of the tile uses are skipped:
+  // their A rows are all zero.  Rows are multiplied independently, so the
+  // result of a row does not depend on which other rows share its tile.
+  if (tid == 0) *used_s = 0;
   if constexpr (PRE)
     for (int i = tid; i < 2 * Cin; i += kBlock) pre_s[i] = pre[i];
-  __syncthreads();
-  for (int i = tid; i < (te - tb) * BM; i += kBlock) {
-    const int t = i / BM, r = i - t * BM;
-    int32_t nb = -1;
-    if (row0 + r < n_out) nb = nbr[(tb + t) * ldn + (rows ? rows[row0 + r] : row0 + r)];
-    nbt[i] = nb;
-    if (nb >= 0) tflag[t] = 1;
-  }
-  __syncthreads();
-  // The used taps in order.  fp32: every thread packs them itself, 4 bits
-  // each (no serial list, one barrier fewer).  bf16: one thread lists them
-  // in LDS; the packed form costs the 128 x 128 tile enough registers to
-  // lose a wave per SIMD.
-  uint64_t tpack = 0;
-  int ntaps = 0;
-  if constexpr (BF16) {
-    if (tid == 0) {
-      int k = 0;
-      for (int t = 0; t < te - tb; ++t)
-        if (tflag[t]) tlist[k++] = t;
-      tlist[15] = k;
+  constexpr int kTapStep = kBlock / BM > 0 ? kBlock / BM : 1;   // taps looked up side by side
+  constexpr int kLook = (kTaps + kTapStep - 1) / kTapStep;
+  {
+    const int r = tid % BM, t0 = tid / BM;
+    const bool in_tile = row0 + r < n_out;
+    const int64_t v = in_tile ? (rows ? rows[row0 + r] : row0 + r) : 0;
+    int32_t nb[kLook];
+#pragma unroll
+    for (int q = 0; q < kLook; ++q) {
+      const int t = t0 + q * kTapStep;
+      nb[q] = t < kTaps && in_tile ? nbr[t * ldn + v] : -1;
     }
-    __syncthreads();
-    ntaps = tlist[15];
-  } else {
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < kLook; ++q) {
+      const int t = t0 + q * kTapStep;
+      if (nb[q] >= 0) mine |= 1u << t;
+      if (t < kTaps) {
+        if constexpr (BUF)
+          nbt[t * BM + r] = nb[q] >= 0 ? static_cast<int32_t>(nb[q] * ld_in * static_cast<int64_t>(sizeof(E))) : kOutOfRange;
+        else
+          nbt[t * BM + r] = nb[q];
+      }
+    }
+    // the wave's taps, one lane each
+    uint32_t wave_used = 0;
 #pragma unroll
     for (int t = 0; t < kTaps; ++t)
-      if (t < te - tb && tflag[t]) {
-        tpack |= static_cast<uint64_t>(t) << (4 * ntaps);
-        ++ntaps;
-      }
-    // the same for every thread: keep it in scalar registers
-    tpack = (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(tpack >> 32))) << 32) |
-            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(tpack)));
-    ntaps = __builtin_amdgcn_readfirstlane(ntaps);
+      if (__ballot((mine >> t) & 1u)) wave_used |= 1u << t;
+    __syncthreads();
+    if (lane == 0 && wave_used) atomicOr(used_s, wave_used);
   }
-  auto tap_at = [&](int ti) {
-    if constexpr (BF16) return static_cast<int>(tlist[ti]);
-    else return static_cast<int>((tpack >> (4 * ti)) & 15);
-  };
-
+  __syncthreads();
+  // taps still to be fetched, in order (the same for every thread: scalar)
+  uint32_t todo = __builtin_amdgcn_readfirstlane(*used_s);
   const int kc_steps = (Cin + P::KC - 1) / P::KC;
-  const int stages = ntaps * kc_steps;
+  const int stages = __builtin_popcount(todo) * kc_steps;
 
   // global -> register copies of one stage.  Every load is issued, also for
   // a missing neighbour, a channel past Cin or a stage past the last: with
-  // buffer loads (BUF) such a load gets an offset beyond the buffer and
-  // reads zeros without touching memory; otherwise it reads a valid address
-  // and the value is replaced by zeros.  With no load skipped, the number of
-  // loads in flight is known, and the wait before a stage is copied to LDS
-  // covers that stage's loads only, not the ones issued after it.
+  // buffer loads such a load gets an offset beyond the buffer and reads zeros
+  // without touching memory.  With no load skipped, the number of loads in
+  // flight is known, and the wait before a stage is copied to LDS covers that
+  // stage's loads only, not the ones issued after it.
   using V = uint4;
-  V ra[NS][P::A_PER_T], rb[NS][P::B_PER_T];
-  // (unused without BUF, where the byte counts are 0)
+  struct Stage {
+    V a[P::A_PER_T], b[P::B_PER_T];
+    int32_t nb[PRE ? P::A_PER_T : 1];   // PRE: the rows' table entries (negative: missing)
+    int kc;
+  };
   const __amdgpu_buffer_rsrc_t rin =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(in), 0, static_cast<int>(in_bytes), kRsrcWord3);
   const __amdgpu_buffer_rsrc_t rw =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(W), 0, static_cast<int>(w_bytes), kRsrcWord3);
-  auto load16 = [&](const __amdgpu_buffer_rsrc_t& rs, const void* base, int64_t elem, bool ok) -> V {
-    if constexpr (BUF) {
-      const int off = ok ? static_cast<int>(elem * static_cast<int64_t>(sizeof(E))) : kOutOfRange;
-      return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-    } else {
-      const V x = *reinterpret_cast<const V*>(static_cast<const E*>(base) + (ok ? elem : 0));
-      return ok ? x : make_uint4(0u, 0u, 0u, 0u);
-    }
+  // chunk cc of rows r0, r0 + kBlock / CPR, ... is this thread's
+  const int cc = tid % P::CPR, cr = tid / P::CPR;
+  constexpr int kRowStep = kBlock / P::CPR;
+  const int cch = cc * P::EPC;
+  int32_t boff[P::B_PER_T];   // byte offset of the weight rows' chunk (BUF), or the row times Cin
+#pragma unroll
+  for (int j = 0; j < P::B_PER_T; ++j) {
+    const int col = col0 + cr + j * kRowStep;
+    if constexpr (BUF) boff[j] = col < Cout ? (col * Cin + cch) * P::U : kOutOfRange;
+    else boff[j] = col < Cout ? col : -1;
+  }
+  int32_t arow[P::A_PER_T];   // table entries of the next stage to fetch,
+  int ft = 0, fkc = 0;        // its tap and first channel
+  auto look = [&]() {
+    ft = todo ? __builtin_ctz(todo) : 0;
+#pragma unroll
+    for (int j = 0; j < P::A_PER_T; ++j) arow[j] = nbt[ft * BM + cr + j * kRowStep];
   };
-  auto fetch = [&](auto set_c, int st) {
-    constexpr int set = decltype(set_c)::value;
-    const bool live = st < stages;
-    const int ti = min(st / kc_steps, 15);
-    const int t = live ? tap_at(ti) : 0;
-    const int kc = (st - ti * kc_steps) * P::KC;
+  look();
+  auto fetch = [&](Stage& s) {
+    // sign bit set where nothing is to be read.  (Opaque to the compiler: as a
+    // condition it makes branches of the loads, and each branch waits for every
+    // load in flight.)
+    int32_t off_bit = todo != 0 && fkc + cch < Cin ? 0 : kOutOfRange;
+    asm volatile("" : "+v"(off_bit));
+    s.kc = fkc;
 #pragma unroll
     for (int j = 0; j < P::A_PER_T; ++j) {
-      const int q = tid + j * kBlock;
-      const int r = q / P::CPR, cc = q % P::CPR;
-      const int ch = kc + cc * P::EPC;
-      const int32_t nb = nbt[t * BM + r];
-      ra[set][j] = load16(rin, in, static_cast<int64_t>(nb) * ld_in + ch, live && nb >= 0 && ch < Cin);
+      if constexpr (BUF) {
+        s.a[j] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rin, (arow[j] + cch * P::U) | off_bit,
+                                                                              fkc * P::U, 0));
+      } else {
+        const bool on = (arow[j] | off_bit) >= 0;
+        const V x = *reinterpret_cast<const V*>(static_cast<const E*>(in) + (on ? arow[j] * ld_in + fkc + cch : 0));
+        s.a[j] = on ? x : make_uint4(0u, 0u, 0u, 0u);
+      }
+      if constexpr (PRE) s.nb[j] = arow[j] | off_bit;
     }
 #pragma unroll
     for (int j = 0; j < P::B_PER_T; ++j) {
-      const int q = tid + j * kBlock;
-      const int r = q / P::CPR, cc = q % P::CPR;
-      const int ch = kc + cc * P::EPC;
-      const int col = col0 + r;
-      rb[set][j] = load16(rw, W, (static_cast<int64_t>(tb + t) * Cout + col) * Cin + ch,
-                          live && q < BN * P::CPR && col < Cout && ch < Cin);
+      if constexpr (BUF) {
+        s.b[j] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rw, boff[j] | off_bit,
+                                                                              (ft * Cout * Cin + fkc) * P::U, 0));
+      } else {
+        const bool on = (boff[j] | off_bit) >= 0;
+        const V x = *reinterpret_cast<const V*>(static_cast<const E*>(W) +
+                                                (on ? (static_cast<int64_t>(ft) * Cout + boff[j]) * Cin + fkc + cch : 0));
+        s.b[j] = on ? x : make_uint4(0u, 0u, 0u, 0u);
+      }
     }
+    // the next stage: further channels of the tap, or the next tap
+    fkc += P::KC;
+    const bool wrap = fkc >= Cin;
+    fkc = wrap ? 0 : fkc;
+    todo = wrap ? todo & (todo - 1) : todo;
+    look();
   };
-  // stage st's copy from its register set to LDS buffer buf
-  auto stash = [&](auto set_c, int buf, int st) {
-    constexpr int set = decltype(set_c)::value;
+  // a stage's copy from its registers to LDS buffer buf
+  auto stash = [&](const Stage& s, int buf) {
     E* a = As + buf * (BM * P::LDR);
     E* bb = Bs + buf * (BN * P::LDR);
-    int t = 0, kc = 0;
+    float sc[P::EPC], sh[P::EPC];
     if constexpr (PRE) {
-      const int ti = min(st / kc_steps, 15);
-      t = st < stages ? tap_at(ti) : 0;
-      kc = (st - ti * kc_steps) * P::KC;
+      const int ch = min(s.kc + cch, Cin - P::EPC);   // (past Cin: not used)
+#pragma unroll
+      for (int i = 0; i < P::EPC; i += 4) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(pre_s + ch + i), y = *reinterpret_cast<const f32x4*>(pre_s + Cin + ch + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          sc[i + q] = x[q];
+          sh[i + q] = y[q];
+        }
+      }
     }
 #pragma unroll
     for (int j = 0; j < P::A_PER_T; ++j) {
-      const int q = tid + j * kBlock;
-      const int r = q / P::CPR, cc = q % P::CPR;
-      V v = ra[set][j];
+      V v = s.a[j];
       if constexpr (PRE) {
-        const int ch = kc + cc * P::EPC;
-        if (st < stages && nbt[t * BM + r] >= 0 && ch < Cin) {
-          uint32_t w[4] = {v.x, v.y, v.z, v.w};
-          if constexpr (BF16) {
+        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        const bool on = s.nb[j] >= 0;
+        if constexpr (BF16) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float lo = fmaxf(fmaf(__uint_as_float(w[i] << 16), pre_s[ch + 2 * i], pre_s[Cin + ch + 2 * i]), 0.f);
-              const float hi = fmaxf(fmaf(__uint_as_float(w[i] & 0xffff0000u), pre_s[ch + 2 * i + 1],
-                                          pre_s[Cin + ch + 2 * i + 1]), 0.f);
-              w[i] = pack_bf16x2(lo, hi);
-            }
-          } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              w[i] = __float_as_uint(fmaxf(fmaf(__uint_as_float(w[i]), pre_s[ch + i], pre_s[Cin + ch + i]), 0.f));
+          for (int i = 0; i < 4; ++i) {
+            const float lo = fmaxf(fmaf(__uint_as_float(w[i] << 16), sc[2 * i], sh[2 * i]), 0.f);
+            const float hi = fmaxf(fmaf(__uint_as_float(w[i] & 0xffff0000u), sc[2 * i + 1], sh[2 * i + 1]), 0.f);
+            w[i] = on ? pack_bf16x2(lo, hi) : 0u;
           }
-          v = make_uint4(w[0], w[1], w[2], w[3]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            w[i] = on ? __float_as_uint(fmaxf(fmaf(__uint_as_float(w[i]), sc[i], sh[i]), 0.f)) : 0u;
         }
+        v = make_uint4(w[0], w[1], w[2], w[3]);
       }
-      *reinterpret_cast<V*>(a + P::at(r, cc)) = v;
+      *reinterpret_cast<V*>(a + P::at(cr + j * kRowStep, cc)) = v;
     }
 #pragma unroll
-    for (int j = 0; j < P::B_PER_T; ++j) {
-      const int q = tid + j * kBlock;
-      if (q < BN * P::CPR) {
-        const int r = q / P::CPR, cc = q % P::CPR;
-        *reinterpret_cast<V*>(bb + P::at(r, cc)) = rb[set][j];
-      }
-    }
+    for (int j = 0; j < P::B_PER_T; ++j) *reinterpret_cast<V*>(bb + P::at(cr + j * kRowStep, cc)) = s.b[j];
   };
 
+  // the lane's output rows
+  int32_t out_row[P::RM];
+#pragma unroll
+  for (int i = 0; i < P::RM; ++i) {
+    const int64_t r = row0 + (wm * P::RM + i) * 16 + li;
+    out_row[i] = r < n_out ? (rows ? rows[r] : static_cast<int32_t>(r)) : -1;
+  }
+
+  // The products take the weights as their first operand, so that lane (i, g)
+  // receives the 4 consecutive output channels 4 g .. 4 g + 3 of row i.
   f32x4 acc[P::RM][P::RN];
 #pragma unroll
   for (int a = 0; a < P::RM; ++a)
 #pragma unroll
     for (int c = 0; c < P::RN; ++c) acc[a][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // NS stages of global loads in flight: stage st is multiplied from LDS
-  // buffer st & 1 while stages st+1 .. st+NS-1 wait in register sets
-  // (st+i) % NS.  After the multiply, stage st+1 goes to the other LDS
-  // buffer and stage st+NS is loaded into the set that stage st vacated, so
-  // a load has NS-1 steps to arrive.  Set indices are compile-time constants
-  // so that the register sets stay in registers.
-  static_for<NS>([&](auto i_c) { fetch(i_c, decltype(i_c)::value); });
-  stash(std::integral_constant<int, 0>{}, 0, 0);
-  __syncthreads();
-  // One pipeline step: stage st is multiplied from LDS buffer st & 1; stage
-  // st+1 goes from its register set to the other buffer and stage st+NS is
-  // loaded into the set stage st vacated.  With SCHED 1 the copy and the
-  // loads come first, so that they overlap the multiply.  All fragments of
-  // the stage are read from LDS before the first MFMA.
-  auto step = [&](auto set_c, int st) {
-    constexpr int SET = decltype(set_c)::value;
-    constexpr int NEXT = (SET + 1) % NS;
-    const int buf = st & 1;
-    if constexpr (SCHED == 1) {
-      stash(std::integral_constant<int, NEXT>{}, buf ^ 1, st + 1);
-      fetch(set_c, st + NS);
+  // rows of a fragment are 16-aligned blocks plus li, so the permutation
+  // of the lane's row is that of li: MFMA step k reads chunk 4 k + lg
+  const E* a_base = As + (wm * P::RM * 16 + li) * P::LDR;
+  const E* b_base = Bs + (wn * P::RN * 16 + li) * P::LDR;
+  const int sw = P::swz(li);
+  constexpr int NK = P::KC / P::KS;
+  constexpr int N0 = (NK + 1) / 2, N1 = NK - N0;   // MFMA steps in the two halves of a stage
+  struct Half {
+    Frag<BF16> a[N0][P::RM], b[N0][P::RN];
+  };
+  // fragments of MFMA steps [K0, K0 + N) of LDS buffer buf
+  auto read = [&](Half& h, int buf, auto k0_c, auto n_c) {
+    constexpr int K0 = decltype(k0_c)::value, N = decltype(n_c)::value;
+    const E* a = a_base + buf * (BM * P::LDR);
+    const E* bb = b_base + buf * (BN * P::LDR);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int ck = (((4 * (K0 + k) + lg) ^ sw) & (P::CPR - 1)) * P::EPC;
+#pragma unroll
+      for (int i = 0; i < P::RM; ++i) h.a[k][i].load(a, i * 16 * P::LDR + ck);
+#pragma unroll
+      for (int j = 0; j < P::RN; ++j) h.b[k][j].load(bb, j * 16 * P::LDR + ck);
     }
-    // rows of a fragment are 16-aligned blocks plus li, so the permutation
-    // of the lane's row is that of li: MFMA step k reads chunk 4 k + lg
-    const E* a = As + buf * (BM * P::LDR) + (wm * P::RM * 16 + li) * P::LDR;
-    const E* bb = Bs + buf * (BN * P::LDR) + (wn * P::RN * 16 + li) * P::LDR;
-    const int sw = P::swz(li);
-    constexpr int NK = P::KC / P::KS;
-    Frag<BF16> fa[NK][P::RM], fb[NK][P::RN];
+  };
+  auto multiply = [&](const Half& h, auto n_c) {
+    constexpr int N = decltype(n_c)::value;
 #pragma unroll
-    for (int k = 0; k < NK; ++k) {
-      const int ck = (((4 * k + lg) ^ sw) & (P::CPR - 1)) * P::EPC;
-#pragma unroll
-      for (int i = 0; i < P::RM; ++i) fa[k][i].load(a, i * 16 * P::LDR + ck);
-#pragma unroll
-      for (int j = 0; j < P::RN; ++j) fb[k][j].load(bb, j * 16 * P::LDR + ck);
-    }
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
+    for (int k = 0; k < N; ++k) {
       if constexpr (BF16) {
 #pragma unroll
         for (int i = 0; i < P::RM; ++i)
 #pragma unroll
-          for (int j = 0; j < P::RN; ++j) mma(acc[i][j], fa[k][i], fb[k][j]);
+          for (int j = 0; j < P::RN; ++j) mma(acc[i][j], h.b[k][j], h.a[k][i]);
       } else {
         // interleave independent accumulators between dependent MFMAs
 #pragma unroll
@@ -480,104 +504,101 @@ k_conv_lds(const int32_t* __restrict__ nbr, int64_t ldn, int64_t n_out, const vo
           for (int i = 0; i < P::RM; ++i)
 #pragma unroll
             for (int j = 0; j < P::RN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[k][i].v[e], fb[k][j].v[e], acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(h.b[k][j].v[e], h.a[k][i].v[e], acc[i][j], 0, 0, 0);
       }
     }
-    if constexpr (SCHED == 0) {
-      // unconditional: past the last stage these copy and load zeros
-      stash(std::integral_constant<int, NEXT>{}, buf ^ 1, st + 1);
-      fetch(set_c, st + NS);
+  };
+  // One step of the pipeline: stage st is multiplied from LDS buffer st & 1 in
+  // two halves whose fragments are read one half ahead, stage st + 2 is
+  // requested, and stage st + 1 (requested a step ago) goes to the other
+  // buffer.  Between the multiplications of a half, which keep the matrix core
+  // busy for 32 (fp32) or 16 cycles each, the wave issues the half's other
+  // instructions; the scheduling groups below ask for that order.
+  Stage ss[NS];
+  Half h0, h1;
+  using C0 = std::integral_constant<int, 0>;
+  using CN0 = std::integral_constant<int, N0>;
+  using CN1 = std::integral_constant<int, N1>;
+  static_for<NS>([&](auto i_c) { fetch(ss[decltype(i_c)::value]); });
+  stash(ss[0], 0);
+  __syncthreads();
+  read(h0, 0, C0{}, CN0{});
+  constexpr int kMfma0 = N0 * P::RM * P::RN * (BF16 ? 1 : 4);
+  constexpr int kReads1 = N1 * (P::RM + P::RN);
+  constexpr int kLoads = P::A_PER_T + P::B_PER_T;
+  auto step = [&](Stage& mine, Stage& next, int buf) {
+    fetch(mine);
+    if constexpr (N1 > 0) read(h1, buf, CN0{}, CN1{});
+    stash(next, buf ^ 1);
+    multiply(h0, CN0{});
+    if constexpr (BUF) {
+      // per MFMA: one load or fragment read, then the copy to LDS
+      constexpr int kSlots = kLoads + kReads1 + kLoads;
+      static_for<kMfma0>([&](auto m_c) {
+        constexpr int m = decltype(m_c)::value;
+        constexpr int q0 = m * kSlots / kMfma0, q1 = (m + 1) * kSlots / kMfma0;
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        static_for<q1 - q0>([&](auto q_c) {
+          constexpr int q = q0 + decltype(q_c)::value;
+          if constexpr (q < kLoads) {
+            __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+          } else if constexpr (q < kLoads + kReads1) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          } else {
+            __builtin_amdgcn_sched_group_barrier(0x2, PRE ? 12 : 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+          }
+        });
+      });
     }
     __syncthreads();
+    read(h0, buf ^ 1, C0{}, CN0{});
+    if constexpr (N1 > 0) multiply(h1, CN1{});
   };
-  // whole groups of NS steps without branches, then the remaining steps
+  // whole groups of NS steps without branches, then the remaining stages
+  static_assert(NS % 2 == 0, "a group of steps leaves the LDS buffers as it found them");
   int st = 0;
   for (; st + NS <= stages; st += NS)
-    static_for<NS>([&](auto i_c) { step(i_c, st + decltype(i_c)::value); });
-  static_for<NS>([&](auto i_c) {
-    if (st + decltype(i_c)::value < stages) step(i_c, st + decltype(i_c)::value);
+    static_for<NS>([&](auto i_c) {
+      constexpr int i = decltype(i_c)::value;
+      step(ss[i], ss[(i + 1) % NS], i & 1);
+    });
+  static_for<NS - 1>([&](auto i_c) {
+    constexpr int i = decltype(i_c)::value;
+    if (st + i < stages) step(ss[i], ss[(i + 1) % NS], i & 1);
   });
 
-  if (part) {
-    // raw partial sums of this split, [split][n_out][Cout]
-    float* dst = part + static_cast<int64_t>(blockIdx.z) * n_out * Cout;
+#pragma unroll
+  for (int i = 0; i < P::RM; ++i) {
+    if (out_row[i] < 0) continue;
+    const int64_t row = out_row[i];
 #pragma unroll
     for (int j = 0; j < P::RN; ++j) {
-      const int col = col0 + (wn * P::RN + j) * 16 + li;
+      const int col = col0 + (wn * P::RN + j) * 16 + 4 * lg;
       if (col >= Cout) continue;
-#pragma unroll
-      for (int i = 0; i < P::RM; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t row = row0 + (wm * P::RM + i) * 16 + lg * 4 + r;
-          if (row < n_out) dst[row * Cout + col] = acc[i][j][r];
-        }
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < P::RN; ++j) {
-    const int col = col0 + (wn * P::RN + j) * 16 + li;
-    if (col >= Cout) continue;
-    const float bv = bias ? bias[col] : 0.f;
-#pragma unroll
-    for (int i = 0; i < P::RM; ++i)
+      float v[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t r0 = row0 + (wm * P::RM + i) * 16 + lg * 4 + r;
-        if (r0 >= n_out) continue;
-        const int64_t row = rows ? rows[r0] : r0;
-        float v = acc[i][j][r] + bv;
-        if (relu) v = fmaxf(v, 0.f);
-        if constexpr (BF16) {
-          if (res) v += __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t*>(res)[row * ld_res + col]) << 16);
-          static_cast<uint16_t*>(out)[row * ld_out + col] = f32_to_bf16(v);
-        } else {
-          if (res) v += static_cast<const float*>(res)[row * ld_res + col];
-          static_cast<float*>(out)[row * ld_out + col] = v;
+        v[r] = acc[i][j][r] + (bias ? bias[col + r] : 0.f);
+        if (relu) v[r] = fmaxf(v[r], 0.f);
+      }
+      if constexpr (BF16) {
+        if (res) {
+          const uint2 x = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(res) + row * ld_res + col);
+          v[0] += __uint_as_float(x.x << 16);
+          v[1] += __uint_as_float(x.x & 0xffff0000u);
+          v[2] += __uint_as_float(x.y << 16);
+          v[3] += __uint_as_float(x.y & 0xffff0000u);
         }
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + row * ld_out + col) =
+            make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+      } else {
+        if (res) {
+          const float4 x = *reinterpret_cast<const float4*>(static_cast<const float*>(res) + row * ld_res + col);
+          v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+        }
+        *reinterpret_cast<float4*>(static_cast<float*>(out) + row * ld_out + col) = make_float4(v[0], v[1], v[2], v[3]);
       }
-  }
-}
-
-// Sum of the split partials in split order, then bias, ReLU and conversion.
-// Partial row r belongs to output row rows[r] when the tiles ran over a row
-// order.
-template <bool BF16>
-__global__ void __launch_bounds__(kBlock)
-k_conv_reduce(const float* __restrict__ part, int splits, int64_t n_out, int Cout, const float* __restrict__ bias,
-              int relu, void* __restrict__ out, int64_t ld_out, const void* __restrict__ res, int64_t ld_res,
-              const int32_t* __restrict__ rows) {
-  const int64_t quads = n_out * (Cout / 4);
-  const int64_t plane = n_out * Cout;
-  for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < quads;
-       q += static_cast<int64_t>(gridDim.x) * kBlock) {
-    const int64_t prow = q / (Cout / 4);
-    const int col = static_cast<int>(q - prow * (Cout / 4)) * 4;
-    float4 a = *reinterpret_cast<const float4*>(part + prow * Cout + col);
-    for (int z = 1; z < splits; ++z) {
-      const float4 b = *reinterpret_cast<const float4*>(part + z * plane + prow * Cout + col);
-      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-    }
-    const int64_t row = rows ? rows[prow] : prow;
-    float v[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (bias) v[i] += bias[col + i];
-      if (relu) v[i] = fmaxf(v[i], 0.f);
-      if (res) {
-        if constexpr (BF16)
-          v[i] += __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t*>(res)[row * ld_res + col + i]) << 16);
-        else
-          v[i] += static_cast<const float*>(res)[row * ld_res + col + i];
-      }
-    }
-    if constexpr (BF16) {
-      const uint32_t lo = pack_bf16x2(v[0], v[1]);
-      const uint32_t hi = pack_bf16x2(v[2], v[3]);
-      *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + row * ld_out + col) = make_uint2(lo, hi);
-    } else {
-      *reinterpret_cast<float4*>(static_cast<float*>(out) + row * ld_out + col) = make_float4(v[0], v[1], v[2], v[3]);
     }
   }
 }
@@ -588,51 +609,46 @@ struct ConvExtent {
   bool buffer_ok() const { return in_bytes <= kMaxBufferBytes && w_bytes <= kMaxBufferBytes; }
 };
 
-template <bool BF16, int BM, int BN, int WM, int WN, int KCB, int NS = 2, bool BUF = true, int SCHED = 0,
-          bool PRE = false>
+template <bool BF16, int BM, int BN, int WM, int WN, int KCB, int NS, bool PRE, bool BUF = true>
 void conv_lds_launch(const int32_t* nbr, int64_t ldn, int64_t n_out, const void* in, int64_t ld_in,
                      int Cin, const void* W, const float* bias, int Cout, int relu, void* out,
-                     int64_t ld_out, const int32_t* rows, ConvExtent ext, hipStream_t s, const float* pre = nullptr,
-                     const void* res = nullptr, int64_t ld_res = 0, int splits = 1, float* part = nullptr) {
+                     int64_t ld_out, const int32_t* rows, ConvExtent ext, hipStream_t s, const float* pre,
+                     const void* res, int64_t ld_res) {
   using P = LdsConv<BF16, BM, BN, WM, WN, KCB>;
   const int lds = P::LDS_BYTES + (PRE ? 8 * Cin : 0);
   static bool lds_limit_set = false;
   if (!lds_limit_set) {
-    (void)hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&k_conv_lds<BF16, BM, BN, WM, WN, KCB, NS, BUF, SCHED, PRE>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, P::LDS_BYTES + (PRE ? 8 * kMaxPreChannels : 0));
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_lds<BF16, BM, BN, WM, WN, KCB, NS, BUF, PRE>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                              P::LDS_BYTES + (PRE ? 8 * kMaxPreChannels : 0));
     lds_limit_set = true;
   }
   const int64_t tiles = (n_out + BM - 1) / BM;
   const int64_t items = tiles * ((Cout + BN - 1) / BN);
   const unsigned per_xcd = static_cast<unsigned>((items + 7) / 8);
-  const dim3 grid(per_xcd * 8, 1, static_cast<unsigned>(splits));
-  launch((k_conv_lds<BF16, BM, BN, WM, WN, KCB, NS, BUF, SCHED, PRE>), grid, dim3(kBlock), static_cast<uint32_t>(lds),
+  launch((k_conv_lds<BF16, BM, BN, WM, WN, KCB, NS, BUF, PRE>), dim3(per_xcd * 8), dim3(kBlock), static_cast<uint32_t>(lds),
          s, nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, static_cast<unsigned>(tiles),
-         splits, splits > 1 ? part : nullptr, static_cast<uint32_t>(BUF ? ext.in_bytes : 0),
-         static_cast<uint32_t>(BUF ? ext.w_bytes : 0), pre, res, ld_res);
-  if (splits > 1) {
-    const int64_t quads = n_out * (Cout / 4);
-    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((quads + kBlock - 1) / kBlock, 8192));
-    launch((k_conv_reduce<BF16>), dim3(blocks), dim3(kBlock), 0, s, part, splits, n_out, Cout, bias,
-                       relu, out, ld_out, res, ld_res, rows);
-  }
+         static_cast<uint32_t>(BUF ? ext.in_bytes : 0), static_cast<uint32_t>(BUF ? ext.w_bytes : 0), pre, res, ld_res);
 }
 
 int64_t blocks_of(int64_t n_out, int Cout, int rows, int cols) {
   return ((n_out + rows - 1) / rows) * ((Cout + cols - 1) / cols);
 }
 
-// Tile choice, from a sweep of tile shapes, pipeline depths and step
-// schedules over the lattices of the LiDAR scan (fp32) and of the 1M-point
-// room (bf16) on MI355X.  fp32: small tiles win; the levels are small and a
-// stage costs several times its MFMA time.  Around a thousand 32 x 32 tiles
-// a third stage in flight (with half the channels per stage) pays; a few
-// hundred 32 x 64 tiles do best with two stages of 64 channels.  bf16: 128 x 128 tiles halve the
-// gathered bytes per flop and win once there are enough of them (wide
-// layers, large levels); 128 x 64 with stages of 32 channels for 64 output
-// channels on large levels (half the weight rows per output row); 64 x 64
-// otherwise.
+// Tile choice, from sweeps over the lattices of a LiDAR scan and of rooms on
+// MI355X (us per convolution; tile rows x columns / bytes of channels a stage).
+// fp32: at 900 tiles of 32 x 64 and more, stages of 32 channels (128->128 on 16k
+// vertices: 48 against 53 for 64-channel stages and for 32 x 32; 128->64 Upsample
+// into 212k: 60 against 75 and 63); from 500 tiles 64-channel stages (256->256 on
+// 6.4k vertices: 67 against 73 and 79); below that, 32 x 32 tiles, as more
+// workgroups matter more than the operand bytes per product (128->128 on 6.4k: 26
+// against 28; 256->256 on 2.2k: 44 against 49).  64 x 64 tiles were slower
+// everywhere (down to one workgroup per compute unit, nothing hides a wave's own
+// waits).  bf16: 128 x 128 tiles halve the gathered bytes per product and win
+// once there are enough of them (wide layers, large levels), with four stages
+// in flight (256->256 on 239k vertices: 1137 against 1226 us for the ResNet block);
+// 128 x 64 for 64 output channels on large levels (half the weight rows per
+// output row); 64 x 64 otherwise.
 // PRE (the pre-activated convolution) uses the same tiles, apart from the
 // register kernel for narrow outputs, which has no pre-activation.
 template <bool BF16, bool PRE>
@@ -642,42 +658,32 @@ void conv_dispatch(const int32_t* nbr, int64_t ldn, int64_t n_out, const void* i
                    const void* res, int64_t ld_res) {
   if (!PRE && !res && Cout <= 16)
     return conv_launch<BF16, 1, 1, 4, 1>(nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, s);
+  auto go = [&](auto bm, auto bn, auto wm, auto wn, auto kcb, auto ns) {
+    conv_lds_launch<BF16, decltype(bm)::value, decltype(bn)::value, decltype(wm)::value, decltype(wn)::value,
+                    decltype(kcb)::value, decltype(ns)::value, PRE>(nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows,
+                                               ext, s, pre, res, ld_res);
+  };
+#define CONV_GO(BM, BN, WM, WN, KCB, NS)                                                                               \
+  return go(std::integral_constant<int, BM>{}, std::integral_constant<int, BN>{}, std::integral_constant<int, WM>{},  \
+            std::integral_constant<int, WN>{}, std::integral_constant<int, KCB>{}, std::integral_constant<int, NS>{})
   if (!ext.buffer_ok())  // operands beyond the reach of a buffer resource
-    return conv_lds_launch<BF16, 64, 64, 2, 2, 128, 2, false, 0, PRE>(
-        nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
+    return conv_lds_launch<BF16, 64, 64, 2, 2, 128, 2, PRE, false>(nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out,
+                                                                ld_out, rows, ext, s, pre, res, ld_res);
   if constexpr (BF16) {
     const int64_t b128 = blocks_of(n_out, Cout, 128, 128);
     const int64_t b64 = blocks_of(n_out, Cout, 64, 64);
-    if (Cout >= 128 && (b128 >= 1500 || (Cin >= 256 && Cout % 128 == 0)))
-      return conv_lds_launch<true, 128, 128, 2, 2, 64, 3, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    if (Cout == 64 && b64 >= 8192)
-      return conv_lds_launch<true, 128, 64, 2, 2, 64, 3, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    if (Cout > 32 && b64 >= 8192)
-      return conv_lds_launch<true, 64, 64, 2, 2, 128, 3, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    if (Cout > 32 && b64 >= 256)
-      return conv_lds_launch<true, 64, 64, 2, 2, 128, 2, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    return conv_lds_launch<true, 32, 32, 2, 2, 128, 2, true, 0, PRE>(
-        nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
+    if (Cout >= 128 && (b128 >= 1500 || (Cin >= 256 && Cout % 128 == 0))) CONV_GO(128, 128, 2, 2, 64, 4);
+    if (Cout == 64 && b64 >= 8192) CONV_GO(128, 64, 2, 2, 64, 2);
+    if (Cout > 32 && b64 >= 256) CONV_GO(64, 64, 2, 2, 128, 2);
+    CONV_GO(32, 32, 2, 2, 128, 2);
   } else {
-    if (Cout > 32 && blocks_of(n_out, Cout, 64, 64) >= 2048)
-      return conv_lds_launch<false, 64, 64, 2, 2, 128, 3, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    if (Cout > 64 && blocks_of(n_out, Cout, 32, 64) >= 1024)
-      return conv_lds_launch<false, 32, 64, 2, 2, 128, 3, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    if (Cout > 64 && blocks_of(n_out, Cout, 32, 64) >= 400)
-      return conv_lds_launch<false, 32, 64, 2, 2, 256, 2, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    if (blocks_of(n_out, Cout, 32, 32) >= 1024)
-      return conv_lds_launch<false, 32, 32, 2, 2, 128, 3, true, 1, PRE>(
-          nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
-    return conv_lds_launch<false, 32, 32, 2, 2, 256, 2, true, 1, PRE>(
-        nbr, ldn, n_out, in, ld_in, Cin, W, bias, Cout, relu, out, ld_out, rows, ext, s, pre, res, ld_res);
+    const int64_t b32x64 = blocks_of(n_out, Cout, 32, 64);
+    if (Cout > 32 && b32x64 >= 900) CONV_GO(32, 64, 2, 2, 128, 2);
+    if (Cout > 32 && b32x64 >= 500) CONV_GO(32, 64, 2, 2, 256, 2);
+    if (blocks_of(n_out, Cout, 32, 32) >= 1024) CONV_GO(32, 32, 2, 2, 128, 2);
+    CONV_GO(32, 32, 2, 2, 256, 2);
   }
+#undef CONV_GO
 }
 
 }  // namespace

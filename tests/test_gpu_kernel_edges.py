@@ -66,3 +66,38 @@ def test_distribute_backward_tiles(L, O, m, cf, widths, clump):  # noqa: F811
     F = rng.normal(size=(m, cf)).astype(np.float32) if cf else None
     gl, ol, g2o = _pair(L, O, pos, 0.1)
     _distribute_backward_case(L, O, gl, ol, g2o, pos, F, widths, m)
+
+
+# convolution: rows and columns that do not fill a tile, channels that do not fill a stage, odd and even stage counts,
+# every tile of the dispatch that a small lattice reaches
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,cin,cout,pre", [(1, 8, 24, False), (40, 40, 40, True), (300, 72, 136, False),
+                                            (900, 136, 72, True), (5000, 64, 128, True), (9000, 32, 320, False)])
+def test_conv_tiles(L, O, m, cin, cout, pre, dtype):  # noqa: F811
+    gl, ol, g2o = _pair(L, O, _cloud(2300 + m, m, 0.7), 0.05)
+    gc, oc = gl.coarsen(), ol.coarsen()
+    g2o_c = P.key_permutation(_host(gc.keys()), oc.keys())
+    rng = np.random.default_rng(m)
+    bf = dtype == "bf16"
+    tol = P.TOL_BF16 if bf else P.TOL_F32
+    rnd = O.round_bf16 if bf else (lambda a: np.asarray(a, np.float32))
+    dev = (lambda a: _dev(np.asarray(a, np.float32), torch.bfloat16)) if bf else (lambda a: _dev(np.asarray(a, np.float32)))
+    W = rnd(rng.normal(size=(9, cin, cout)) / np.sqrt(9 * cin))
+    gW = dev(np.ascontiguousarray(np.transpose(W, (0, 2, 1))))
+    bias = (0.3 * rng.normal(size=cout)).astype(np.float32)
+    for gd, gs, od, os_, pd, ps, up in ((gl, gl, ol, ol, g2o, g2o, False), (gc, gl, oc, ol, g2o_c, g2o, False),
+                                        (gl, gc, ol, oc, g2o, g2o_c, True)):
+        X = rnd(rng.normal(size=(os_.n, cin)))
+        R = rnd(rng.normal(size=(od.n, cout)))
+        A = X.astype(np.float64)
+        if pre:
+            A = O.groupnorm(A, 4, eps=1e-5, relu=True)
+            A = O.round_bf16(A).astype(np.float64) if bf else A
+        ref = (od.refine_into if up else od.conv)(os_, A, W.astype(np.float64), bias=bias.astype(np.float64), relu=True)
+        if pre:
+            res = None if up else dev(R[pd])
+            got = gd.conv_preact(gs, dev(X[ps]), gW, groups=4, bias=_dev(bias), relu=True, refine=up, res=res)
+            ref = ref if up else ref + R
+        else:
+            got = (gd.refine if up else gd.conv)(gs, dev(X[ps]), gW, bias=_dev(bias), relu=True)
+        P.assert_close(P.rows_in_oracle_order(_host(got), pd), rnd(ref), tol, f"m={m} {cin}->{cout} {dtype} pre={pre} up={up}")
