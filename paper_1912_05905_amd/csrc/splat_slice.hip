@@ -16,6 +16,8 @@ constexpr int kBlock = 256;
 constexpr int64_t kDeformBwdGrid = 1024;   // workgroups of the DeformSlice backward's per-point pass
 constexpr unsigned kClassifyGrid = 2048;   // workgroups of the fused classifier (a multiple of 8)
 constexpr int kClassifyMaxWeights = 16384; // K x C classifier weights staged in LDS
+constexpr int kClassifyTileC = 256;        // widest rows whose LDS tiles leave room for the weights
+constexpr int kClassifyMaxLds = 160 * 1024;
 
 // float -> bfloat16, round to nearest even (NaN stays NaN).
 // Row / chunk index of a lane group with XCD-contiguous workgroup order:
@@ -125,6 +127,26 @@ template <> struct Chunk<true> {
     for (int i = 0; i < 4; ++i)
       w[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
     *reinterpret_cast<uint4*>(static_cast<uint16_t*>(base) + elem) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+};
+
+// The same chunk as loaded, widened when it is used.
+template <bool BF16> struct Raw {
+  uint4 u;
+  __device__ inline void load(const void* base, int64_t elem) {
+    u = *reinterpret_cast<const uint4*>(static_cast<const char*>(base) + elem * (BF16 ? 2 : 4));
+  }
+  __device__ inline void widen(Chunk<BF16>& c) const {
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (BF16) {
+        c.v[2 * i] = __uint_as_float(w[i] << 16);
+        c.v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+      } else {
+        c.v[i] = __uint_as_float(w[i]);
+      }
+    }
   }
 };
 
@@ -662,143 +684,339 @@ k_deform_slice(const int4* __restrict__ idx, const float4* __restrict__ w, int64
   }
 }
 
-// lanes per row: enough 16-byte chunks to cover C, at most 64 (a wavefront)
-// One exchange of the reduce-scatter in k_deform_classify: lanes whose bit
-// OFF is set keep the upper LEN values, the others the lower LEN, and each
-// adds the half its partner gives away.
-// One exchange of the reduce-scatter in k_deform_classify: lanes whose bit
-// OFF is set keep the upper LEN values, the others the lower LEN, and each
-// adds the half its partner gives away.
+// DeformSlice fused with the last linear classification layer
+// (Implementation): logits = Wc f + bc for the DeformSlice rows f, which are
+// never stored.  The classes run on v_mfma_f32_16x16x4_f32 with Wc (LDS, in
+// fragment order) as one operand and f as the other; lane (i, g) of the product
+// receives the classes 4 g .. 4 g + 3 of point i, per 16 classes.
+// What bounds it are the vector operations on the gathered values (22 per
+// channel of a point); with every lane reading all K weight rows of its
+// channels from LDS and the K partial sums exchanged over the row's lanes, the
+// classes cost more than that: C = 128, 20 classes, 1M points bf16 took 532 us
+// and 120k points fp32 75 us, and 218 and 42 us here (with every lane keeping 8
+// channels of the four rows of one of 16 points, and no tile, 250: a wave per SIMD).
+typedef float f32x4_v __attribute__((ext_vector_type(4)));
 
-// One exchange of the reduce-scatter in k_deform_classify: lanes whose bit
-// OFF is set keep the upper LEN values, the others the lower LEN, and each
-// adds the half its partner gives away; blk gathers the kept halves' bits.
-template <int OFF, int LEN, int KP>
-__device__ inline void reduce_scatter_step(float (&lg)[KP], int lane, int& blk) {
-  const bool up = (lane & OFF) != 0;
-#pragma unroll
-  for (int i = 0; i < LEN; ++i) {
-    const float give = up ? lg[i] : lg[i + LEN];
-    const float keep = up ? lg[i + LEN] : lg[i];
-    lg[i] = keep + xor_lane<OFF>(give);
+// Wc in LDS: [block of 16 channels][nb][lane][4], the class 16 nb + i and the
+// channel 4 g + e of the block in lane (i, g)
+__device__ inline void stage_classifier(float* wl, const float* __restrict__ Wc, int K, int C, int blocks, int NB) {
+  for (int i = threadIdx.x; i < blocks * NB * 256; i += kBlock) {
+    const int e = i & 3, L = (i >> 2) & 63, run = i >> 8;
+    const int nb = run % NB, cb = run / NB;
+    const int cls = 16 * nb + (L & 15), ch = 16 * cb + 4 * (L >> 4) + e;
+    wl[i] = cls < K && ch < C ? Wc[cls * C + ch] : 0.f;
   }
-  blk = 2 * blk + (up ? 1 : 0);
 }
 
+// Sums over the channels in short chains (a single chain through the products
+// doubles the rounding error): four chains, one per channel of a lane's four,
+// over kClassifyRun blocks of 16 channels, then added to the total.
+constexpr int kClassifyRun = 2;
+template <int NB>
+struct ClassSums {
+  f32x4_v run[4][NB], total[NB];
+  __device__ ClassSums() {
+    clear();
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) total[nb] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ inline void clear() {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) run[e][nb] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ inline void add(const f32x4_v (&w)[NB], int e, float f) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) run[e][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][e], f, run[e][nb], 0, 0, 0);
+  }
+  __device__ inline void flush() {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) total[nb] += (run[0][nb] + run[1][nb]) + (run[2][nb] + run[3][nb]);
+    clear();
+  }
+};
 
-// DeformSlice fused with the last linear classification layer
-// (Implementation): the DeformSlice row of a point is formed in registers as
-// in k_deform_slice and multiplied by Wc (K x C, staged in LDS); the KP >= K
-// logit partials of a lane group are summed by a reduce-scatter, after which
-// each lane holds KP / LPR finished classes (the block its exchange bits
-// name).  The high-dimensional per-point row is never stored.
-template <bool BF16, int LPR, int CPL, int KP>
+// the lane's 4 classes of point p
+template <int NB>
+__device__ inline void store_classes(float* __restrict__ out, int64_t p, int K, int lg, int vec_out,
+                                     const f32x4_v (&acc)[NB]) {
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int j = 16 * nb + 4 * lg;
+    float* o = out + p * K + j;
+    if (vec_out) {
+      if (j < K) *reinterpret_cast<f32x4_v*>(o) = acc[nb];
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (j + r < K) o[r] = acc[nb][r];
+    }
+  }
+}
+
+// Rows of at most kClassifyTileC channels: a point's row is gathered by LPR
+// lanes as in k_deform_slice (whole rows a load), TP points (at least 16) in
+// turn, and f goes through a tile in LDS into the product's operand layout.
+// Every load is issued, from a valid address (a condition would make branches
+// of the loads, each waiting for all in flight): a vertex slot without a vertex
+// (a lattice the build flagged) reads row 0 with weight and coefficient 0,
+// channels past C the row's last ones, against zeros in wvec and Wc.
+template <bool BF16, int LPR, int CPL, int NB>
 __global__ void __launch_bounds__(kBlock)
 k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
                   const void* __restrict__ vals, int64_t ld_vals, int C, const float* __restrict__ wvec, float beta,
                   const float* __restrict__ Wc, const float* __restrict__ bc, int K, float* __restrict__ out,
-                  unsigned nblk) {
+                  int vec_out, unsigned nblk) {
   using Ch = Chunk<BF16>;
-  extern __shared__ __align__(16) float wl[];   // [K][C]
-  for (int i = threadIdx.x; i < K * C; i += kBlock) wl[i] = Wc[i];
+  constexpr int EPL = Ch::N;
+  constexpr int PPS = 64 / LPR;                 // points per step
+  constexpr int TP = PPS > 16 ? PPS : 16;       // points per tile
+  constexpr int CW = LPR * CPL * EPL;           // channels of a tile, zero-padded
+  constexpr int PITCH = CW + 4;
+  constexpr int BLK = (CW + 15) / 16;
+  extern __shared__ __align__(16) float wl[];   // Wc, then the waves' tiles [TP][PITCH]
+  stage_classifier(wl, Wc, K, C, BLK, NB);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  const int pl = lane / LPR, cl = lane & (LPR - 1);   // point of a step, lane of its row
+  float* T = wl + BLK * NB * 256 + wave * TP * PITCH;
+  float wv[CPL][EPL];
+#pragma unroll
+  for (int q = 0; q < CPL; ++q)
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const int ch = (cl + q * LPR) * EPL + i;
+      wv[q][i] = ch < C ? wvec[ch] : 0.f;
+    }
+  f32x4_v bias[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = 16 * nb + 4 * lg + r;
+      bias[nb][r] = bc && j < K ? bc[j] : 0.f;
+    }
   __syncthreads();
-  const int lane = threadIdx.x & (LPR - 1);
-  const int nchunk = C / Ch::N;
   // The weights are staged once per workgroup, which then walks a
-  // contiguous range of the nblk logical blocks (each XCD a contiguous
+  // contiguous range of the nblk groups of 4 TP points (each XCD a contiguous
   // share of the ranges, as xcd_item).
   const unsigned G = gridDim.x;   // a multiple of 8
-  const unsigned r = (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8;
+  const unsigned rg = (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8;
   const unsigned per = (nblk + G - 1) / G;
-  const unsigned lb1 = min((r + 1) * per, nblk);
-  for (unsigned lb = r * per; lb < lb1; ++lb) {
-  const int64_t p = (static_cast<int64_t>(lb) * kBlock + threadIdx.x) / LPR;
-  const bool live = p < m;
-  int4 iv = make_int4(-1, -1, -1, -1);
-  float4 wq = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (live) { iv = idx[p]; wq = w[p]; }
-  const int32_t vi[4] = {iv.x, iv.y, iv.z, iv.w};
-  const float bw[4] = {wq.x, wq.y, wq.z, wq.w};
-  float x[CPL][4][Ch::N];
-  float part[4] = {0.f, 0.f, 0.f, 0.f};
+  const unsigned lb1 = min((rg + 1) * per, nblk);
+  // Steps are pipelined over the tiles: while one is computed, the rows of the
+  // next are on their way and the vertices of the one after it.
+  constexpr int STEPS = TP / PPS;
+  const unsigned lb0 = rg * per;
+  auto point = [&](unsigned step) {
+    const int64_t tile = static_cast<int64_t>(lb0 + step / STEPS) * 4 + wave;
+    return min(tile * TP + static_cast<int64_t>(step % STEPS) * PPS + pl, m - 1);
+  };
+  Raw<BF16> xn[CPL][4];
+  auto gather = [&](const int4& v) {
+    const int32_t vi[4] = {max(v.x, 0), max(v.y, 0), max(v.z, 0), max(v.w, 0)};
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    const int ch = lane + q * LPR;
-    const bool on = live && ch < nchunk;
+    for (int q = 0; q < CPL; ++q) {
+      const int ch = min((cl + q * LPR) * EPL, C - EPL);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (on && vi[k] >= 0) {
-        Ch c;
-        c.load(vals, static_cast<int64_t>(vi[k]) * ld_vals + static_cast<int64_t>(ch) * Ch::N);
+      for (int k = 0; k < 4; ++k) xn[q][k].load(vals, static_cast<int64_t>(vi[k]) * ld_vals + ch);
+    }
+  };
+  int4 iv = idx[point(0)], iv_next = idx[point(1)];
+  float4 wq = w[point(0)], wq_next = w[point(1)];
+  if (lb0 < lb1) gather(iv);
+  unsigned step = 0;
+  for (unsigned lb = lb0; lb < lb1; ++lb) {
+    const int64_t p0 = (static_cast<int64_t>(lb) * 4 + wave) * TP;
+#pragma unroll 1
+    for (int st = 0; st < STEPS; ++st, ++step) {
+      const bool have[4] = {iv.x >= 0, iv.y >= 0, iv.z >= 0, iv.w >= 0};
+      const float bw[4] = {have[0] ? wq.x : 0.f, have[1] ? wq.y : 0.f, have[2] ? wq.z : 0.f, have[3] ? wq.w : 0.f};
+      Ch x[CPL][4];
 #pragma unroll
-        for (int i = 0; i < Ch::N; ++i) x[q][k][i] = c.v[i];
+      for (int q = 0; q < CPL; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xn[q][k].widen(x[q][k]);
+      iv = iv_next;
+      wq = wq_next;
+      gather(iv);
+      iv_next = idx[point(step + 2)];
+      wq_next = w[point(step + 2)];
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < CPL; ++q)
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          float qk[4];
+          float mx = -INFINITY;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            qk[k] = bw[k] * x[q][k].v[i];
+            mx = fmaxf(mx, qk[k]);
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) part[k] += (qk[k] - mx) * wv[q][i];
+        }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part[k] = group_sum<LPR>(part[k]);
+      float coef[4];
+      if constexpr (LPR >= 4) {
+        // lane 4 j + k of the row takes the k-th offset, the quad exchanges them
+        const int k = lane & 3;
+        const float mine = tanhf(beta + (k == 0 ? part[0] : (k == 1 ? part[1] : (k == 2 ? part[2] : part[3]))));
+        const int x4 = __float_as_int(mine);
+        coef[0] = __int_as_float(__builtin_amdgcn_update_dpp(0, x4, 0x00, 0xF, 0xF, false));
+        coef[1] = __int_as_float(__builtin_amdgcn_update_dpp(0, x4, 0x55, 0xF, 0xF, false));
+        coef[2] = __int_as_float(__builtin_amdgcn_update_dpp(0, x4, 0xAA, 0xF, 0xF, false));
+        coef[3] = __int_as_float(__builtin_amdgcn_update_dpp(0, x4, 0xFF, 0xF, 0xF, false));
       } else {
 #pragma unroll
-        for (int i = 0; i < Ch::N; ++i) x[q][k][i] = 0.f;
+        for (int k = 0; k < 4; ++k) coef[k] = tanhf(beta + part[k]);
       }
-    }
-    if (on) {
 #pragma unroll
-      for (int i = 0; i < Ch::N; ++i) {
-        const float wc = wvec[ch * Ch::N + i];
+      for (int k = 0; k < 4; ++k) coef[k] = have[k] ? bw[k] + coef[k] : 0.f;
+      float* row = T + (st * PPS + pl) * PITCH;
+#pragma unroll
+      for (int q = 0; q < CPL; ++q)
+#pragma unroll
+        for (int i = 0; i < EPL; i += 4) {
+          f32x4_v f;
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            f[u] = coef[0] * x[q][0].v[i + u] + coef[1] * x[q][1].v[i + u] + coef[2] * x[q][2].v[i + u] +
+                   coef[3] * x[q][3].v[i + u];
+          *reinterpret_cast<f32x4_v*>(row + (cl + q * LPR) * EPL + i) = f;
+        }
+    }
+    // a wave's LDS accesses take effect in order; the fences keep the compiler
+    // from moving the reads above the writes, and the next tile's writes above
+    // the reads
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int mg = 0; mg < TP / 16; ++mg) {
+      ClassSums<NB> sums;
+      const float* f = T + (mg * 16 + li) * PITCH + 4 * lg;
+      const f32x4_v* wf = reinterpret_cast<const f32x4_v*>(wl) + lane;
+#pragma unroll 1
+      for (int c0 = 0; c0 < BLK; c0 += kClassifyRun) {
+#pragma unroll
+        for (int cb = c0; cb < c0 + kClassifyRun; ++cb) {
+          if (BLK % kClassifyRun != 0 && cb >= BLK) break;
+          f32x4_v x = {0.f, 0.f, 0.f, 0.f};
+          if (CW % 16 == 0 || 16 * cb + 4 * lg < CW) x = *reinterpret_cast<const f32x4_v*>(f + 16 * cb);
+          f32x4_v wr[NB];
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) wr[nb] = wf[(cb * NB + nb) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sums.add(wr, e, x[e]);
+        }
+        sums.flush();
+      }
+      f32x4_v acc[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[nb] = sums.total[nb] + bias[nb];
+      const int64_t p = p0 + mg * 16 + li;
+      if (p < m) store_classes<NB>(out, p, K, lg, vec_out, acc);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+// Wider rows: lane (i, g) holds, of the gathered rows of point i, the channels
+// 4 g .. 4 g + 3 of 16 channels at a time, which are the product's operand as
+// they are; the rows are gathered once for the offsets and again for f.
+template <bool BF16, int NB>
+__global__ void __launch_bounds__(kBlock)
+k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
+                       const void* __restrict__ vals, int64_t ld_vals, int C, const float* __restrict__ wvec,
+                       float beta, const float* __restrict__ Wc, const float* __restrict__ bc, int K,
+                       float* __restrict__ out, int vec_out, unsigned nblk) {
+  extern __shared__ __align__(16) float wl[];   // Wc, then wvec
+  const int blocks = (C + 15) / 16;
+  float* const wvl = wl + blocks * NB * 256;
+  stage_classifier(wl, Wc, K, C, blocks, NB);
+  for (int i = threadIdx.x; i < blocks * 16; i += kBlock) wvl[i] = i < C ? wvec[i] : 0.f;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  f32x4_v bias[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = 16 * nb + 4 * lg + r;
+      bias[nb][r] = bc && j < K ? bc[j] : 0.f;
+    }
+  const unsigned G = gridDim.x;   // a multiple of 8
+  const unsigned rg = (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8;
+  const unsigned per = (nblk + G - 1) / G;
+  const unsigned lb1 = min((rg + 1) * per, nblk);
+  for (unsigned lb = rg * per; lb < lb1; ++lb) {
+    const int64_t p = (static_cast<int64_t>(lb) * 4 + wave) * 16 + li;
+    const int4 iv = idx[min(p, m - 1)];
+    const float4 wq = w[min(p, m - 1)];
+    const int32_t vi[4] = {max(iv.x, 0), max(iv.y, 0), max(iv.z, 0), max(iv.w, 0)};
+    const bool have[4] = {iv.x >= 0, iv.y >= 0, iv.z >= 0, iv.w >= 0};
+    const float bw[4] = {have[0] ? wq.x : 0.f, have[1] ? wq.y : 0.f, have[2] ? wq.z : 0.f, have[3] ? wq.w : 0.f};
+    auto gather = [&](int cb, f32x4_v (&x)[4]) {
+      const int ch = min(16 * cb + 4 * lg, C - 4);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int64_t at = static_cast<int64_t>(vi[k]) * ld_vals + ch;
+        if constexpr (BF16) {
+          const uint2 u = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(vals) + at);
+          x[k] = f32x4_v{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                         __uint_as_float(u.y & 0xffff0000u)};
+        } else {
+          x[k] = *reinterpret_cast<const f32x4_v*>(static_cast<const float*>(vals) + at);
+        }
+      }
+    };
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int cb = 0; cb < blocks; ++cb) {
+      f32x4_v x[4];
+      gather(cb, x);
+      const f32x4_v wv = *reinterpret_cast<const f32x4_v*>(wvl + 16 * cb + 4 * lg);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
         float qk[4];
         float mx = -INFINITY;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          qk[k] = bw[k] * x[q][k][i];
+          qk[k] = bw[k] * x[k][e];
           mx = fmaxf(mx, qk[k]);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) part[k] += (qk[k] - mx) * wc;
+        for (int k = 0; k < 4; ++k) part[k] += (qk[k] - mx) * wv[e];
       }
     }
-  }
+    float coef[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) part[k] = group_sum<LPR>(part[k]);
-  float coef[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) coef[k] = bw[k] + tanhf(beta + part[k]);
-  float lg[KP];
-#pragma unroll
-  for (int j = 0; j < KP; ++j) lg[j] = 0.f;
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    const int ch = lane + q * LPR;
-    if (!(live && ch < nchunk)) continue;
-#pragma unroll
-    for (int i = 0; i < Ch::N; i += 4) {
-      float f[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        f[u] = coef[0] * x[q][0][i + u] + coef[1] * x[q][1][i + u] + coef[2] * x[q][2][i + u] +
-               coef[3] * x[q][3][i + u];
-#pragma unroll
-      for (int j = 0; j < KP; ++j) {
-        if (j >= K) break;
-        const float4 wv4 = *reinterpret_cast<const float4*>(wl + j * C + ch * Ch::N + i);
-        lg[j] += wv4.x * f[0] + wv4.y * f[1] + wv4.z * f[2] + wv4.w * f[3];
-      }
+    for (int k = 0; k < 4; ++k) {
+      part[k] += xor_lane<16>(part[k]);
+      part[k] += xor_lane<32>(part[k]);
+      coef[k] = have[k] ? bw[k] + tanhf(beta + part[k]) : 0.f;
     }
-  }
-  // the exchanges in the order of their cost (cheap ones move the most
-  // values); blk = the class block this lane keeps
-  int blk = 0;
-  constexpr int S = (LPR >= 2) + (LPR >= 4) + (LPR >= 8) + (LPR >= 16) + (LPR >= 32) + (LPR >= 64);
-  static_assert((KP >> S) >= 1, "at least one class per lane");
-  if constexpr (LPR >= 2) reduce_scatter_step<1, (KP >> 1)>(lg, lane, blk);
-  if constexpr (LPR >= 4) reduce_scatter_step<2, (KP >> 2)>(lg, lane, blk);
-  if constexpr (LPR >= 16) reduce_scatter_step<8, (KP >> 3)>(lg, lane, blk);
-  if constexpr (LPR >= 8) reduce_scatter_step<4, (KP >> (LPR >= 16 ? 4 : 3))>(lg, lane, blk);
-  if constexpr (LPR >= 32) reduce_scatter_step<16, (KP >> 5)>(lg, lane, blk);
-  if constexpr (LPR >= 64) reduce_scatter_step<32, (KP >> 6)>(lg, lane, blk);
-  if (live) {
-    constexpr int OWN = KP / LPR;
+    ClassSums<NB> sums;
+    const f32x4_v* wf = reinterpret_cast<const f32x4_v*>(wl) + lane;
+    for (int cb = 0; cb < blocks; ++cb) {
+      f32x4_v x[4], wr[NB];
+      gather(cb, x);
 #pragma unroll
-    for (int i = 0; i < OWN; ++i) {
-      const int j = blk * OWN + i;
-      if (j < K) out[p * K + j] = lg[i] + (bc ? bc[j] : 0.f);
+      for (int nb = 0; nb < NB; ++nb) wr[nb] = wf[(cb * NB + nb) * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        sums.add(wr, e, coef[0] * x[0][e] + coef[1] * x[1][e] + coef[2] * x[2][e] + coef[3] * x[3][e]);
+      if (cb % kClassifyRun == kClassifyRun - 1) sums.flush();
     }
-  }
+    sums.flush();
+    f32x4_v acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = sums.total[nb] + bias[nb];
+    if (p < m) store_classes<NB>(out, p, K, lg, vec_out, acc);
   }
 }
 
@@ -1139,28 +1357,44 @@ void launch_slice(const int32_t* idx, const float* w, int64_t m, const void* val
   else slice_dispatch<false>(lpr, idx, w, m, vals, ld_vals, C, out, s);
 }
 
-template <bool BF16, int CPL, int KP>
-void deform_classify_dispatch(int lpr, const int32_t* idx, const float* w, int64_t m, const void* vals, int64_t ldv,
-                              int C, const float* wv, float beta, const float* Wc, const float* bc, int K,
-                              float* out, hipStream_t s) {
-  const unsigned nblk = grid_for(m, lpr);
-  const dim3 g(std::min(xcd_grid(nblk), kClassifyGrid)), b(kBlock);
-  const int4* i4 = reinterpret_cast<const int4*>(idx);
-  const float4* w4 = reinterpret_cast<const float4*>(w);
-  const uint32_t lds = static_cast<uint32_t>(4 * K * C);
-#define DCL_CASE(L)                                                                                              \
-  if (lpr == L) {                                                                                                \
-    static bool set = false;                                                                                     \
-    if (!set) {                                                                                                  \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_deform_classify<BF16, L, CPL, KP>),               \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kClassifyMaxWeights);           \
-      set = true;                                                                                                \
-    }                                                                                                            \
-    return launch((k_deform_classify<BF16, L, CPL, KP>), g, b, lds, s, i4, w4, m, vals, ldv, C, wv, beta, Wc, bc, K, \
-                  out, nblk);                                                                                    \
+template <class Kernel>
+void classify_launch(Kernel kernel, bool* limit_set, size_t lds, int points_per_group, const int32_t* idx,
+                     const float* w, int64_t m, const void* vals, int64_t ldv, int C, const float* wv, float beta,
+                     const float* Wc, const float* bc, int K, float* out, hipStream_t s) {
+  if (!*limit_set) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              kClassifyMaxLds);
+    *limit_set = true;
   }
-  if constexpr (KP >= 64) { DCL_CASE(64) }
-  DCL_CASE(1) DCL_CASE(2) DCL_CASE(4) DCL_CASE(8) DCL_CASE(16) DCL_CASE(32)
+  const unsigned nblk = static_cast<unsigned>((m + points_per_group - 1) / points_per_group);
+  const int vec_out = K % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0;
+  launch(kernel, dim3(std::min(xcd_grid(nblk), kClassifyGrid)), dim3(kBlock), static_cast<uint32_t>(lds), s,
+         reinterpret_cast<const int4*>(idx), reinterpret_cast<const float4*>(w), m, vals, ldv, C, wv, beta, Wc, bc, K,
+         out, vec_out, nblk);
+}
+
+template <bool BF16, int NB>
+void deform_classify_dispatch(const int32_t* idx, const float* w, int64_t m, const void* vals, int64_t ldv, int C,
+                              const float* wv, float beta, const float* Wc, const float* bc, int K, float* out,
+                              hipStream_t s) {
+  const int lpr = point_lanes_per_row(C, BF16);
+  const bool two = C / Chunk<BF16>::N > lpr;
+  if (C > kClassifyTileC) {
+    static bool set = false;
+    const size_t blocks = (C + 15) / 16;
+    return classify_launch(&k_deform_classify_wide<BF16, NB>, &set, 4 * (blocks * NB * 256 + blocks * 16), 64, idx, w, m,
+                           vals, ldv, C, wv, beta, Wc, bc, K, out, s);
+  }
+#define DCL_CASE(L, CPL)                                                                                              \
+  if (lpr == L && two == (CPL == 2)) {                                                                                \
+    static bool set = false;                                                                                          \
+    constexpr int TP = 64 / L > 16 ? 64 / L : 16, CW = L * CPL * Chunk<BF16>::N;                                      \
+    return classify_launch(&k_deform_classify<BF16, L, CPL, NB>, &set,                                                \
+                           4 * static_cast<size_t>((CW + 15) / 16 * NB * 256 + 4 * TP * (CW + 4)), 4 * TP, idx, w, m, vals, \
+                           ldv, C, wv, beta, Wc, bc, K, out, s);                                                      \
+  }
+  DCL_CASE(1, 1) DCL_CASE(2, 1) DCL_CASE(4, 1) DCL_CASE(8, 1) DCL_CASE(16, 1) DCL_CASE(32, 1)
+  if constexpr (!BF16) { DCL_CASE(8, 2) DCL_CASE(64, 1) }
 #undef DCL_CASE
 }
 
@@ -1171,21 +1405,19 @@ void launch_deform_classify(const int32_t* idx, const float* w, int64_t m, const
                             int bf16, const float* wv, float beta, const float* Wc, const float* bc, int K, float* out,
                             hipStream_t s) {
   if (m <= 0) return;
-  const int chunks = C / (bf16 ? 8 : 4);
-  const int lpr = point_lanes_per_row(C, bf16 != 0);
   ScopedKernelTimer tm("deform_slice", s);
-  const bool two = chunks > lpr;
-  const bool kp64 = K > 32 || lpr > 32;
-#define DCL_GO(BFV, CPLV)                                                                                          \
-  (kp64 ? deform_classify_dispatch<BFV, CPLV, 64>(lpr, idx, w, m, vals, ld_vals, C, wv, beta, Wc, bc, K, out, s)  \
-        : deform_classify_dispatch<BFV, CPLV, 32>(lpr, idx, w, m, vals, ld_vals, C, wv, beta, Wc, bc, K, out, s))
-  if (bf16) {
-    if (two) DCL_GO(true, 2);
-    else DCL_GO(true, 1);
-  } else {
-    if (two) DCL_GO(false, 2);
-    else DCL_GO(false, 1);
+  const int nb = (K + 15) / 16;   // K <= 64
+#define DCL_GO(BFV, NBV) return deform_classify_dispatch<BFV, NBV>(idx, w, m, vals, ld_vals, C, wv, beta, Wc, bc, K, out, s)
+#define DCL_NB(BFV)              \
+  switch (nb) {                  \
+    case 1: DCL_GO(BFV, 1);      \
+    case 2: DCL_GO(BFV, 2);      \
+    case 3: DCL_GO(BFV, 3);      \
+    default: DCL_GO(BFV, 4);     \
   }
+  if (bf16) DCL_NB(true)
+  else DCL_NB(false)
+#undef DCL_NB
 #undef DCL_GO
 }
 

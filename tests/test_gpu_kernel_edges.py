@@ -101,3 +101,22 @@ def test_conv_tiles(L, O, m, cin, cout, pre, dtype):  # noqa: F811
         else:
             got = (gd.refine if up else gd.conv)(gs, dev(X[ps]), gW, bias=_dev(bias), relu=True)
         P.assert_close(P.rows_in_oracle_order(_host(got), pd), rnd(ref), tol, f"m={m} {cin}->{cout} {dtype} pre={pre} up={up}")
+
+
+# DeformSlice + classifier: 16-point tiles of 1 to 64 lanes per row, 16-class blocks, wide rows, unaligned class counts
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,C,K", [(1, 8, 1), (15, 16, 17), (65, 40, 16), (257, 72, 5), (300, 136, 33), (100, 256, 64),
+                                   (70, 264, 60), (33, 504, 32)])
+def test_classifier_tiles(L, O, m, C, K, dtype):  # noqa: F811
+    gl, ol, g2o = _pair(L, O, _cloud(2400 + m, m, 0.6), 0.1)
+    rng = np.random.default_rng(m)
+    X = rng.normal(size=(ol.n, C))
+    X = O.round_bf16(X) if dtype == "bf16" else X.astype(np.float32)
+    wv = (rng.normal(size=C) / np.sqrt(C)).astype(np.float32)
+    Wc = (rng.normal(size=(K, C)) / np.sqrt(C)).astype(np.float32)
+    bc = rng.normal(size=K).astype(np.float32)
+    ref = ol.deform_slice_classify(X.astype(np.float64), wv.astype(np.float64), 0.1, Wc.astype(np.float64),
+                                   bc.astype(np.float64))
+    x = _dev(np.asarray(X, np.float32)[g2o], torch.bfloat16 if dtype == "bf16" else None)
+    got = gl.deform_slice_classify(x, _dev(wv), 0.1, _dev(Wc), _dev(bc))
+    P.assert_close(_host(got), ref, P.TOL_F32, f"logits m={m} C={C} K={K} {dtype}")
