@@ -120,3 +120,23 @@ def test_classifier_tiles(L, O, m, C, K, dtype):  # noqa: F811
     x = _dev(np.asarray(X, np.float32)[g2o], torch.bfloat16 if dtype == "bf16" else None)
     got = gl.deform_slice_classify(x, _dev(wv), 0.1, _dev(Wc), _dev(bc))
     P.assert_close(_host(got), ref, P.TOL_F32, f"logits m={m} C={C} K={K} {dtype}")
+
+
+# GroupNorm statistics and their backward: rows around the 32-row parts and 8-row batches, one to 16 row slots
+@pytest.mark.parametrize("m,C,groups", [(2, 8, 2), (12, 64, 32), (40, 256, 32), (700, 128, 4), (1500, 1024, 32)])
+def test_group_norm_parts(L, O, m, C, groups):  # noqa: F811
+    gl, ol, g2o = _pair(L, O, _cloud(2500 + m, m, 0.7), 0.1)
+    rng = np.random.default_rng(m)
+    X = (rng.normal(size=(ol.n, C)) + rng.normal(size=C)).astype(np.float32)
+    W = (rng.normal(size=(9, C, 8)) / np.sqrt(9 * C)).astype(np.float32)
+    dY = rng.normal(size=(ol.n, 8)).astype(np.float32)
+    A = O.groupnorm(X.astype(np.float64), groups, eps=1e-5, relu=True)
+    gW = _dev(np.ascontiguousarray(np.transpose(W, (0, 2, 1))))
+    got = gl.conv_preact(gl, _dev(X[g2o]), gW, groups=groups)
+    P.assert_close(P.rows_in_oracle_order(_host(got), g2o), ol.conv(ol, A, W.astype(np.float64)), P.TOL_F32, f"m={m} C={C}")
+    odA, _, _ = ol.conv_backward(ol, A, W.astype(np.float64), dY.astype(np.float64))
+    odX, odg, odb = O.groupnorm_backward(X.astype(np.float64), odA, groups, eps=1e-5, relu=True)
+    gdX, _, _, gdg, gdb = gl.conv_preact_backward(gl, _dev(X[g2o]), gW, _dev(dY[g2o]), groups=groups)
+    P.assert_close(P.rows_in_oracle_order(_host(gdX), g2o), odX, P.TOL_F32, f"dX m={m} C={C}")
+    P.assert_close(_host(gdg), odg, P.TOL_F32, f"dgamma m={m} C={C}")
+    P.assert_close(_host(gdb), odb, P.TOL_F32, f"dbeta m={m} C={C}")
