@@ -521,6 +521,14 @@ int prepare_build(lattice_s* L, const lattice_s* parent, int64_t cap, hipStream_
   return LAT_OK;
 }
 
+// A table that can be rebuilt larger counts as overflowed once a key finds no
+// slot within this many probes.  Linear probing of a table that fills up takes
+// time that grows with its size (a room of 65,536 points with 142k vertices in
+// 131,072 slots: 428 ms, nearly all of it in the insert), a rebuild about 2 ms.
+// At the loads a table is sized for, up to about 0.8, no probe sequence gets
+// this long.
+constexpr uint64_t kRetryProbes = 2048;
+
 // The insert of level L: from the positions (halved `halvings` times after
 // elevation) or from y_src times y_scale.
 InsertJob insert_job(const lattice_s* L, const float* pos, const float* y_src, float y_scale, int halvings,
@@ -534,6 +542,7 @@ InsertJob insert_job(const lattice_s* L, const float* pos, const float* y_src, f
   j.a1 = a[1];
   j.a2 = a[2];
   j.h = L->hash();
+  j.last_probe = L->retry_cap > L->cap ? std::min(j.h.mask, kRetryProbes - 1) : j.h.mask;
   j.counter = &L->dc->counter;
   j.vkeys = L->vkeys;
   j.vslot = L->vslot;
@@ -641,10 +650,19 @@ int ensure_lists(lattice_s* L, hipStream_t s) {
 }
 
 // Table size for a build: the caller's hint, else 2 slots per point for
-// the first level (surface clouds have at most about one vertex per point)
-// and 2 per parent vertex for coarse levels.  A table that overflows is
-// rebuilt at the worst-case size (2 slots per vertex reference) from the
-// handle's own elevated positions, so no caller buffer is needed again.
+// the first level (dense surface clouds have at most about one vertex per
+// point) and 2 per parent vertex for coarse levels.  Small clouds are sparse
+// on the lattice's scale (2,047-point objects, rooms and scans have 2 to 4
+// vertices per point) and their tables cost little to clear: up to 16,384
+// points the first level's table takes the worst case (2 slots per reference,
+// no overflow), up to 65,536 half of it.  Create + splat with 2 slots per point
+// and with this rule: object of 2,047 points at a load of 0.74 119 and 72 us,
+// and where the table overflowed and was rebuilt at every build, 7.8 and
+// 0.08 ms; rooms of 2,047, 16,384 and 65,536 points 8.4, 85 and 429 ms against
+// 0.09, 0.10 and 0.15; dense clouds (objects and scans of 10,000 to 65,536
+// points) 74 to 97 us either way.  A table that overflows is rebuilt at the
+// worst-case size (2 slots per vertex reference) from the handle's own
+// elevated positions, so no caller buffer is needed again.
 int64_t initial_capacity(const lattice_s* L, const lattice_s* parent, int64_t capacity_hint) {
   const int64_t refs = 4 * L->m;
   const int64_t full = next_pow2(std::max<int64_t>(1024, 2 * refs));
@@ -653,7 +671,8 @@ int64_t initial_capacity(const lattice_s* L, const lattice_s* parent, int64_t ca
   // a finest level, or a coarse one whose parent's count is not read back
   // yet: 2 slots per point (a coarse level has at most about as many
   // vertices as its parent)
-  return std::min(full, next_pow2(std::max<int64_t>(1024, 2 * L->m)));
+  const int64_t slots = parent || L->m > 65536 ? 2 : (L->m > 16384 ? 4 : 8);
+  return std::min(full, next_pow2(std::max<int64_t>(1024, slots * L->m)));
 }
 
 // The library's own stream per device (default priority) on which coarse

@@ -282,7 +282,7 @@ k_insert_points(InsertJobs jobs, int64_t m) {
     if (u < nunique) pending |= 1u << j;
   }
   uint32_t created_mask = 0;
-  for (uint64_t probe = 0; pending != 0 && probe <= h.mask; ++probe) {
+  for (uint64_t probe = 0; pending != 0 && probe <= J.last_probe; ++probe) {
     uint64_t prev[kVerts];
 #pragma unroll
     for (int j = 0; j < kVerts; ++j)

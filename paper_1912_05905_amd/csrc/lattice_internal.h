@@ -167,6 +167,7 @@ struct InsertJob {
   int halvings;
   float a0, a1, a2;
   HashView h;
+  uint64_t last_probe;   // a key that finds no slot by this probe has overflowed the table
   int32_t* counter;
   uint64_t* vkeys;
   int32_t* vslot;

@@ -7,7 +7,8 @@ import numpy as np
 import pytest
 
 from tests import parity as P
-from tests.test_gpu_parity import L, O, _cloud, _dev, _distribute_backward_case, _host, _pair  # noqa: F401
+from tests.test_gpu_parity import (L, O, _check_down_up, _check_structure, _cloud, _dev, _distribute_backward_case, _host,  # noqa: F401
+                                   _pair)
 
 pytestmark = pytest.mark.gpu
 
@@ -140,3 +141,40 @@ def test_group_norm_parts(L, O, m, C, groups):  # noqa: F811
     P.assert_close(P.rows_in_oracle_order(_host(gdX), g2o), odX, P.TOL_F32, f"dX m={m} C={C}")
     P.assert_close(_host(gdg), odg, P.TOL_F32, f"dgamma m={m} C={C}")
     P.assert_close(_host(gdb), odb, P.TOL_F32, f"dbeta m={m} C={C}")
+
+
+# first table by the cloud's size: worst case up to 16,384 points, half of it up to 65,536, then 2 slots per point, where a
+# sparse cloud overflows and is rebuilt (also when another stream asks first, and through coarse levels built before that)
+@pytest.mark.parametrize("m,sigma", [(16_384, 0.002), (16_385, 0.002), (65_536, 0.002), (70_000, 0.001)])
+@pytest.mark.parametrize("hierarchy", [True, False])
+def test_first_table_sizes(L, O, m, sigma, hierarchy):  # noqa: F811
+    pos = _cloud(2600, m, 1.0)
+    ols = [O.Lattice.create(pos, np.full(3, sigma, np.float32))]
+    ols.append(ols[0].coarsen())
+    assert ols[0].n > 3.5 * m
+    F = np.random.default_rng(m).normal(size=(m, 4)).astype(np.float32)
+    pd, Fd = _dev(pos), _dev(F)
+    torch.cuda.synchronize()
+    if hierarchy:
+        gls = L.Lattice.create_hierarchy(pd, [sigma] * 3, 2)
+    else:
+        gls = [L.Lattice.create(pd, [sigma] * 3)]
+        gls.append(gls[0].coarsen())
+    with torch.cuda.stream(torch.cuda.Stream()):
+        got = gls[0].splat(Fd)
+    torch.cuda.synchronize()
+    g2o = [_check_structure(g, o) for g, o in zip(gls, ols)]
+    P.assert_close(P.rows_in_oracle_order(_host(got), g2o[0]), ols[0].splat(F)[0], P.TOL_F32, "splat")
+    _check_down_up(np.random.default_rng(m), g2o, gls, ols)
+    for g in reversed(gls):
+        g.destroy()
+
+
+# a hinted table is not rebuilt: it may fill up, however long the probe sequences get
+def test_hinted_table_nearly_full(L, O):  # noqa: F811
+    pos = _cloud(2601, 2040, 1.0)
+    ol = O.Lattice.create(pos, np.full(3, 0.002, np.float32))
+    assert 0.98 * 8192 < ol.n <= 8192
+    gl = L.Lattice.create(_dev(pos), [0.002] * 3, capacity_hint=4096)
+    _check_structure(gl, ol)
+    gl.destroy()
