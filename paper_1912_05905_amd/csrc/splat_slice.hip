@@ -586,6 +586,77 @@ k_slice(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
   }
 }
 
+// Slice of rows wider than 64 channels: a wave takes whole points, PP
+// consecutive ones, a lane V consecutive channels of each.  Indices, weights
+// and row addresses are then the same for the wave and are read and computed
+// by the scalar unit.  What bounds the slice of wide rows is the sum of its
+// vector operations, its gathers through the L1 (195 us alone for 1M points of
+// 256 bf16 channels) and its stores (220 us alone); this takes the addresses
+// and the weights' selects off the vector unit and stores whole lines: 380 us with lane groups, 342
+// here (128 channels of 200k points: 44 and 40).  More points a wave, a loop
+// over points and other orders of the blocks made no difference.
+// Up to 64 channels a wave would have less than 4 bytes a lane to load, and
+// the lane groups of k_slice stay.
+template <bool BF16, int V>
+__global__ void __launch_bounds__(kBlock)
+k_slice_wide(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
+             const void* __restrict__ vals, int64_t ld_vals, int C, float* __restrict__ out, unsigned nblk) {
+  constexpr int PP = BF16 ? 4 : 2;
+  typedef float OutV __attribute__((ext_vector_type(V)));
+  using Raw = typename std::conditional<BF16, typename std::conditional<V == 4, uint2, uint32_t>::type, OutV>::type;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const unsigned per = (nblk + 7) / 8;
+  const int64_t block = static_cast<int64_t>(blockIdx.x % 8) * per + blockIdx.x / 8;   // as xcd_item
+  const int64_t p0 = PP * (block * (kBlock / 64) + wave);
+  if (p0 >= m) return;
+  int64_t row[PP][4];
+  float bw[PP][4];
+#pragma unroll
+  for (int u = 0; u < PP; ++u) {
+    const int64_t p = min(p0 + u, m - 1);
+    const int4 iv = idx[p];
+    const float4 wv = w[p];
+    const int32_t v[4] = {iv.x, iv.y, iv.z, iv.w};
+    const float b[4] = {wv.x, wv.y, wv.z, wv.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {   // (a slot without a vertex: row 0 with weight 0)
+      row[u][k] = max(v[k], 0) * ld_vals;
+      bw[u][k] = v[k] < 0 ? 0.f : b[k];
+    }
+  }
+  using E = typename std::conditional<BF16, uint16_t, float>::type;
+  for (int ch = V * lane; ch < C; ch += 64 * V) {
+    Raw x[PP][4];
+#pragma unroll
+    for (int u = 0; u < PP; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[u][k] = *reinterpret_cast<const Raw*>(static_cast<const E*>(vals) + row[u][k] + ch);
+#pragma unroll
+    for (int u = 0; u < PP; ++u) {
+      if (p0 + u >= m) break;
+      OutV acc = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if constexpr (BF16) {
+          uint32_t q[2];
+          if constexpr (V == 4) { q[0] = x[u][k].x; q[1] = x[u][k].y; }
+          else q[0] = x[u][k];
+#pragma unroll
+          for (int i = 0; i < V; i += 2) {
+            acc[i] += bw[u][k] * __uint_as_float(q[i / 2] << 16);
+            acc[i + 1] += bw[u][k] * __uint_as_float(q[i / 2] & 0xffff0000u);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < V; ++i) acc[i] += bw[u][k] * x[u][k][i];
+        }
+      }
+      __builtin_nontemporal_store(acc, reinterpret_cast<OutV*>(out + (p0 + u) * C + ch));
+    }
+  }
+}
+
 // DeformSlice (Eq. deformSlice): q_k = b_k x_k; M = max_k q_k per channel;
 // db_k = tanh(beta + (q_k - M) . wv); out = sum_k (b_k + db_k) x_k.
 // Each lane keeps its channels of the d+1 gathered rows in registers; the
@@ -1279,6 +1350,14 @@ void deform_bwd_point_dispatch(int lpr, unsigned grid, const int32_t* idx, const
 template <bool BF16>
 void slice_dispatch(int lpr, const int32_t* idx, const float* w, int64_t m, const void* vals,
                     int64_t ldv, int C, float* out, hipStream_t s) {
+  if (C > 64) {   // a wave per point
+    const int64_t per_block = (kBlock / 64) * (BF16 ? 4 : 2);
+    const unsigned nb = static_cast<unsigned>((m + per_block - 1) / per_block);
+    const auto kernel = C > 128 ? k_slice_wide<BF16, 4> : k_slice_wide<BF16, 2>;
+    launch(kernel, dim3(xcd_grid(nb)), dim3(kBlock), 0, s, reinterpret_cast<const int4*>(idx),
+           reinterpret_cast<const float4*>(w), m, vals, ldv, C, out, nb);
+    return;
+  }
   const unsigned nblk = grid_for((m + 1) / 2, lpr);   // two points per lane group
   const dim3 g(xcd_grid(nblk)), b(kBlock);
   const int4* i4 = reinterpret_cast<const int4*>(idx);
@@ -1288,9 +1367,7 @@ void slice_dispatch(int lpr, const int32_t* idx, const float* w, int64_t m, cons
     case 2: launch((k_slice<BF16, 2>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
     case 4: launch((k_slice<BF16, 4>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
     case 8: launch((k_slice<BF16, 8>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
-    case 16: launch((k_slice<BF16, 16>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
-    case 32: launch((k_slice<BF16, 32>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
-    default: launch((k_slice<BF16, 64>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
+    default: launch((k_slice<BF16, 16>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;   // C <= 64
   }
 }
 

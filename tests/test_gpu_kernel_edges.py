@@ -178,3 +178,14 @@ def test_hinted_table_nearly_full(L, O):  # noqa: F811
     gl = L.Lattice.create(_dev(pos), [0.002] * 3, capacity_hint=4096)
     _check_structure(gl, ol)
     gl.destroy()
+
+
+# slice: lane groups up to 64 channels; beyond, a wave per point with 2 or 4 channels a lane, several passes over a row
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,C", [(1, 8), (3, 64), (5, 72), (258, 128), (259, 136), (1023, 264), (77, 1032)])
+def test_slice_tiles(L, O, m, C, dtype):  # noqa: F811
+    gl, ol, g2o = _pair(L, O, _cloud(2700 + m, m, 0.6), 0.1)
+    X = np.random.default_rng(m).normal(size=(ol.n, C))
+    X = O.round_bf16(X) if dtype == "bf16" else X.astype(np.float32)
+    got = gl.slice(_dev(np.asarray(X, np.float32)[g2o], torch.bfloat16 if dtype == "bf16" else None))
+    P.assert_close(_host(got), ol.slice(X.astype(np.float64)), P.TOL_F32, f"m={m} C={C} {dtype}")
