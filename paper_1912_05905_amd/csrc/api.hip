@@ -1560,17 +1560,12 @@ int lattice_splat_backward(lattice_t L, const float* dX_dev, int64_t ld_dX, int 
   if ((st = check_matrix(dF_dev, C, C, LAT_F32, "dF", L->m > 0)) != LAT_OK) return st;
   if (L->m == 0) return LAT_OK;
   ScopedKernelTimer tm("splat_bwd", stream);
-  const float* src = dX_dev;
-  int64_t ld = ld_dX;
-  Scratch scaled;
+  Scratch scale;
   if (normalize) {
-    if ((st = scaled.get(sizeof(float) * static_cast<size_t>(L->n) * C, stream)) != LAT_OK) return st;
-    launch_scale_by_weight_sum(L->offsets, L->entry_w, wsum_dev, L->n, dX_dev, ld_dX, C, scaled.as<float>(), C,
-                               stream);
-    src = scaled.as<float>();
-    ld = C;
+    if ((st = scale.get(sizeof(float) * static_cast<size_t>(L->n), stream)) != LAT_OK) return st;
+    launch_weight_sum_scale(L->offsets, L->entry_w, wsum_dev, L->n, scale.as<float>(), stream);
   }
-  launch_slice(L->idx, L->w, L->m, src, ld, C, false, dF_dev, stream);
+  launch_slice(L->idx, L->w, L->m, dX_dev, ld_dX, C, false, dF_dev, stream, normalize ? scale.as<float>() : nullptr);
   return check_launch("splat backward");
 }
 

@@ -253,7 +253,7 @@ void launch_splat(const int32_t* offsets, const int32_t* entries, const float* e
                   const void* feat, int64_t ld_feat, int C, int bf16, int normalize, void* vals,
                   int64_t ld_vals, float* wsum, float* partials, hipStream_t s);
 void launch_slice(const int32_t* idx, const float* w, int64_t m, const void* vals, int64_t ld_vals,
-                  int C, int bf16, float* out, hipStream_t s);
+                  int C, int bf16, float* out, hipStream_t s, const float* vscale = nullptr);
 void launch_deform_slice(const int32_t* idx, const float* w, int64_t m, const void* vals,
                          int64_t ld_vals, int C, int bf16, const float* wv, float beta, float* out,
                          float* delta, float* plain, hipStream_t s);
@@ -291,8 +291,8 @@ void launch_distribute(const int32_t* offsets, const int32_t* entries, const int
                        const float* b1, int C1, const float* W2, const float* b2, int C2, const float* W3,
                        const float* b3, int C3, void* out, int out_bf16, int64_t ld_out, void* work, hipStream_t s);
 // backward.hip
-void launch_scale_by_weight_sum(const int32_t* offsets, const float* entry_w, const float* wsum, int64_t n,
-                                const float* in, int64_t ld_in, int C, float* out, int64_t ld_out, hipStream_t s);
+void launch_weight_sum_scale(const int32_t* offsets, const float* entry_w, const float* wsum, int64_t n, float* scale,
+                             hipStream_t s);
 // dY, Y, G, W, Wt (and X below) are float32, or bfloat16 with bf16 != 0
 void launch_conv_bwd_prep(const void* dY, int64_t ld_dy, const void* Y, int64_t ld_y, int64_t n, void* G,
                           int64_t ld_g, const void* W, int Cout, int Cin, void* Wt, int bf16, hipStream_t s);

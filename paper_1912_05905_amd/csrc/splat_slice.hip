@@ -538,10 +538,13 @@ k_splat_finish(const int32_t* __restrict__ offsets, const int32_t* __restrict__ 
 // the bytes in flight per lane).  A vertex slot without a vertex (a lattice
 // the build flagged) reads row 0 with weight 0, so that the loads are issued
 // without branches.
-template <bool BF16, int LPR>
+// SCALED: every vertex row is taken times vscale[vertex], which is folded into
+// the weights (the gradient of a normalised splat).
+template <bool BF16, int LPR, bool SCALED>
 __global__ void __launch_bounds__(kBlock)
 k_slice(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
-        const void* __restrict__ vals, int64_t ld_vals, int C, float* __restrict__ out, unsigned nblk) {
+        const void* __restrict__ vals, int64_t ld_vals, int C, float* __restrict__ out,
+        const float* __restrict__ vscale, unsigned nblk) {
   using Ch = Chunk<BF16>;
   constexpr int PP = 2;
   const int lane = threadIdx.x & (LPR - 1);
@@ -559,6 +562,10 @@ k_slice(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
     bw[u][1] = iv.y < 0 ? 0.f : wv.y;
     bw[u][2] = iv.z < 0 ? 0.f : wv.z;
     bw[u][3] = iv.w < 0 ? 0.f : wv.w;
+    if constexpr (SCALED) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) bw[u][k] *= vscale[vi[u][k]];
+    }
   }
   const int nchunk = C / Ch::N;
   for (int ch = lane; ch < nchunk; ch += LPR) {
@@ -597,10 +604,11 @@ k_slice(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
 // over points and other orders of the blocks made no difference.
 // Up to 64 channels a wave would have less than 4 bytes a lane to load, and
 // the lane groups of k_slice stay.
-template <bool BF16, int V>
+template <bool BF16, int V, bool SCALED>
 __global__ void __launch_bounds__(kBlock)
 k_slice_wide(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
-             const void* __restrict__ vals, int64_t ld_vals, int C, float* __restrict__ out, unsigned nblk) {
+             const void* __restrict__ vals, int64_t ld_vals, int C, float* __restrict__ out,
+             const float* __restrict__ vscale, unsigned nblk) {
   constexpr int PP = BF16 ? 4 : 2;
   typedef float OutV __attribute__((ext_vector_type(V)));
   using Raw = typename std::conditional<BF16, typename std::conditional<V == 4, uint2, uint32_t>::type, OutV>::type;
@@ -623,6 +631,7 @@ k_slice_wide(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t
     for (int k = 0; k < 4; ++k) {   // (a slot without a vertex: row 0 with weight 0)
       row[u][k] = max(v[k], 0) * ld_vals;
       bw[u][k] = v[k] < 0 ? 0.f : b[k];
+      if constexpr (SCALED) bw[u][k] *= vscale[max(v[k], 0)];
     }
   }
   using E = typename std::conditional<BF16, uint16_t, float>::type;
@@ -1347,27 +1356,27 @@ void deform_bwd_point_dispatch(int lpr, unsigned grid, const int32_t* idx, const
 #undef DPT_CASE
 }
 
-template <bool BF16>
+template <bool BF16, bool SCALED>
 void slice_dispatch(int lpr, const int32_t* idx, const float* w, int64_t m, const void* vals,
-                    int64_t ldv, int C, float* out, hipStream_t s) {
+                    int64_t ldv, int C, float* out, const float* vscale, hipStream_t s) {
+  const int4* i4 = reinterpret_cast<const int4*>(idx);
+  const float4* w4 = reinterpret_cast<const float4*>(w);
+  const dim3 b(kBlock);
   if (C > 64) {   // a wave per point
     const int64_t per_block = (kBlock / 64) * (BF16 ? 4 : 2);
-    const unsigned nb = static_cast<unsigned>((m + per_block - 1) / per_block);
-    const auto kernel = C > 128 ? k_slice_wide<BF16, 4> : k_slice_wide<BF16, 2>;
-    launch(kernel, dim3(xcd_grid(nb)), dim3(kBlock), 0, s, reinterpret_cast<const int4*>(idx),
-           reinterpret_cast<const float4*>(w), m, vals, ldv, C, out, nb);
+    const unsigned nblk = static_cast<unsigned>((m + per_block - 1) / per_block);
+    const auto kernel = C > 128 ? k_slice_wide<BF16, 4, SCALED> : k_slice_wide<BF16, 2, SCALED>;
+    launch(kernel, dim3(xcd_grid(nblk)), b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk);
     return;
   }
   const unsigned nblk = grid_for((m + 1) / 2, lpr);   // two points per lane group
-  const dim3 g(xcd_grid(nblk)), b(kBlock);
-  const int4* i4 = reinterpret_cast<const int4*>(idx);
-  const float4* w4 = reinterpret_cast<const float4*>(w);
+  const dim3 g(xcd_grid(nblk));
   switch (lpr) {
-    case 1: launch((k_slice<BF16, 1>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
-    case 2: launch((k_slice<BF16, 2>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
-    case 4: launch((k_slice<BF16, 4>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
-    case 8: launch((k_slice<BF16, 8>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;
-    default: launch((k_slice<BF16, 16>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, nblk); break;   // C <= 64
+    case 1: launch((k_slice<BF16, 1, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
+    case 2: launch((k_slice<BF16, 2, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
+    case 4: launch((k_slice<BF16, 4, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
+    case 8: launch((k_slice<BF16, 8, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
+    default: launch((k_slice<BF16, 16, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;   // C <= 64
   }
 }
 
@@ -1426,12 +1435,13 @@ void launch_splat(const int32_t* offsets, const int32_t* entries, const float* e
 }
 
 void launch_slice(const int32_t* idx, const float* w, int64_t m, const void* vals, int64_t ld_vals,
-                  int C, int bf16, float* out, hipStream_t s) {
+                  int C, int bf16, float* out, hipStream_t s, const float* vscale) {
   if (m <= 0) return;
   const int lpr = lanes_per_row(C, bf16 != 0);
   ScopedKernelTimer tm("slice", s);
-  if (bf16) slice_dispatch<true>(lpr, idx, w, m, vals, ld_vals, C, out, s);
-  else slice_dispatch<false>(lpr, idx, w, m, vals, ld_vals, C, out, s);
+  if (bf16) slice_dispatch<true, false>(lpr, idx, w, m, vals, ld_vals, C, out, nullptr, s);
+  else if (vscale) slice_dispatch<false, true>(lpr, idx, w, m, vals, ld_vals, C, out, vscale, s);
+  else slice_dispatch<false, false>(lpr, idx, w, m, vals, ld_vals, C, out, nullptr, s);
 }
 
 template <class Kernel>

@@ -189,3 +189,17 @@ def test_slice_tiles(L, O, m, C, dtype):  # noqa: F811
     X = O.round_bf16(X) if dtype == "bf16" else X.astype(np.float32)
     got = gl.slice(_dev(np.asarray(X, np.float32)[g2o], torch.bfloat16 if dtype == "bf16" else None))
     P.assert_close(_host(got), ol.slice(X.astype(np.float64)), P.TOL_F32, f"m={m} C={C} {dtype}")
+
+
+# gradient of a normalised splat: 1 / (weight sum), given or summed, folded into the slice's weights; lane groups and wave form
+@pytest.mark.parametrize("given", [True, False])
+@pytest.mark.parametrize("m,C", [(1, 4), (3, 8), (17, 16), (65, 64), (258, 68), (259, 128), (515, 132), (77, 516)])
+def test_splat_backward_scales(L, O, m, C, given):  # noqa: F811
+    gl, ol, g2o = _pair(L, O, _cloud(2800 + m, m, 0.6), 0.1)
+    dX = np.random.default_rng(m + C).normal(size=(ol.n, C)).astype(np.float32)
+    ws = None
+    if given:
+        ws = torch.empty(gl.n, device="cuda")
+        gl.splat(_dev(np.ones((m, 4), np.float32)), normalize=True, wsum=ws)
+    got = gl.splat_backward(_dev(dX[g2o]), normalize=True, wsum=ws)
+    P.assert_close(_host(got), ol.splat_backward(dX.astype(np.float64), normalize=True), P.TOL_F32, f"m={m} C={C}")
