@@ -37,9 +37,9 @@ FAMILY_KERNELS = {
     "lists": ["k_fill_lists"], "nbr": ["k_level_tables", "k_mask_order"],
     "deform_bwd": ["k_deform_bwd", "DeformGradRows"],
     "conv_bwd": ["k_conv_wgrad", "k_wgrad_reduce", "k_conv_bwd_prep"], "linear_bwd": ["k_lin_"],
-    "splat_bwd": ["k_scale_by_weight_sum"], "groupnorm": ["k_gn_"],
+    "splat_bwd": ["k_weight_sum_scale"], "groupnorm": ["k_gn_"],
     "splat": ["k_splat_chunks", "k_splat_finish"], "distribute": ["k_dist_"], "conv": ["k_conv"],
-    "slice": ["k_slice<"],
+    "slice": ["k_slice<", "k_slice_wide"],
     "deform_slice": ["k_deform_slice", "k_deform_classify"],
 }
 CSRC = os.path.join(ROOT, "paper_1912_05905_amd", "csrc")
