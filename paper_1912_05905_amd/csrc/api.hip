@@ -977,7 +977,7 @@ int conv_common(const int32_t* table, int64_t ldn, int64_t n_out, int64_t n_in, 
   if (gn) {
     // the statistics of the input lattice's rows, then the convolution
     if ((st = pre.get(sizeof(float) * 2 * static_cast<size_t>(Cin), s)) != LAT_OK) return st;
-    if ((st = work.get(static_cast<size_t>(gn_workspace_bytes(n_in, Cin)), s)) != LAT_OK) return st;
+    if ((st = work.get(static_cast<size_t>(gn_workspace_bytes(n_in, Cin, dt == LAT_BF16)), s)) != LAT_OK) return st;
     launch_gn_affine(in, ld_in, Cin, dt == LAT_BF16, n_in, gn->groups, gn->gamma, gn->beta, gn->eps,
                      pre.as<float>(), work.p, s);
   }
@@ -1728,7 +1728,7 @@ int lattice_conv_preact_backward(lattice_t dst, lattice_t src, const float* X_de
   Scratch pre, stats, work, act, dact, coef;
   if ((st = pre.get(sizeof(float) * 2 * static_cast<size_t>(Cin), stream)) != LAT_OK) return st;
   if ((st = stats.get(sizeof(double) * 2 * static_cast<size_t>(groups), stream)) != LAT_OK) return st;
-  if ((st = work.get(static_cast<size_t>(gn_workspace_bytes(n_in, Cin)), stream)) != LAT_OK) return st;
+  if ((st = work.get(static_cast<size_t>(gn_workspace_bytes(n_in, Cin, 0)), stream)) != LAT_OK) return st;
   if ((st = act.get(sizeof(float) * std::max<size_t>(nc, 4), stream)) != LAT_OK) return st;
   if (need_dA && (st = dact.get(sizeof(float) * std::max<size_t>(nc, 4), stream)) != LAT_OK) return st;
   if ((st = coef.get(sizeof(float) * 4 * static_cast<size_t>(Cin), stream)) != LAT_OK) return st;

@@ -1270,7 +1270,7 @@ namespace {
 // statistics partials: of the raw rows, of a layer's outputs (one per
 // workgroup of k_dist_fwd64), of the GroupNorm backward
 int64_t backward_stats_bytes(int64_t total, int64_t widest) {
-  return std::max<int64_t>(gn_workspace_bytes(total, static_cast<int>(widest)),
+  return std::max<int64_t>(gn_workspace_bytes(total, static_cast<int>(widest), 0),
                            std::max<int64_t>(kStatsMaxParts, mlp_grid(total)) * 2 * widest * 8);
 }
 }  // namespace

@@ -312,7 +312,10 @@ void launch_conv(const int32_t* nbr, int64_t ldn, int64_t n_out, int64_t n_in, c
 int conv_max_pre_channels();
 // norm.hip
 int gn_max_channels();
-int64_t gn_workspace_bytes(int64_t n, int C);
+// partials (2 C doubles each) of launch_gn_affine on n rows of this dtype, and
+// of launch_gn_backward (fp32), and the work space they take
+int64_t gn_partials(int64_t n, int C, int bf16);
+int64_t gn_workspace_bytes(int64_t n, int C, int bf16);
 // stats (optional): per group the mean and 1 / sqrt(var + eps), as doubles
 void launch_gn_affine(const void* x, int64_t ld, int C, int bf16, int64_t n, int groups, const float* gamma,
                       const float* beta, float eps, float* pre, void* work, hipStream_t s, double* stats = nullptr);
@@ -343,7 +346,7 @@ void launch_gn_relu_apply(const float* x, int64_t ldx, int C, int64_t n, const f
                           hipStream_t s);
 // GroupNorm + ReLU backward from dA = dL/d(pre-activated input): dgamma,
 // dbeta (optional, C floats), dX (optional, n x C, row stride lddx); coef
-// is a 4 C float work array; work holds gn_workspace_bytes(n, C).  The ReLU
+// is a 4 C float work array; work holds gn_workspace_bytes(n, C, 0).  The ReLU
 // passed where act > 0 when the forward's activations act (n x C, row
 // stride ldact) are given, else where x pre[c] + pre[C + c] > 0.  With
 // xhat the rows x are given already normalised ((x - mean_g) inv_g).

@@ -387,10 +387,14 @@ void launch_gn_finalize(const double* part, int64_t nparts, int C, int groups, i
 
 int gn_max_channels() { return 4 * kBlock; }
 
-int64_t gn_workspace_bytes(int64_t n, int C) {
+int64_t gn_partials(int64_t n, int C, int bf16) {
   int64_t np, rp;
-  gn_parts(n, C, 0, &np, &rp);   // fp32 splits into at least as many parts as bf16
-  return np * 2 * C * static_cast<int64_t>(sizeof(double));
+  gn_parts(n, C, bf16, &np, &rp);
+  return np;
+}
+
+int64_t gn_workspace_bytes(int64_t n, int C, int bf16) {
+  return gn_partials(n, C, bf16) * 2 * C * static_cast<int64_t>(sizeof(double));
 }
 
 void launch_gn_affine(const void* x, int64_t ld, int C, int bf16, int64_t n, int groups, const float* gamma,

@@ -143,6 +143,20 @@ def test_group_norm_parts(L, O, m, C, groups):  # noqa: F811
     P.assert_close(_host(gdb), odb, P.TOL_F32, f"dbeta m={m} C={C}")
 
 
+# bf16 GroupNorm statistics at widths whose bf16 rows split into more parts than fp32 rows (33 rows a part against 35)
+@pytest.mark.parametrize("m,C,groups", [(14, 176, 8), (60, 176, 4), (60, 184, 8), (700, 184, 4), (60, 136, 8)])
+def test_group_norm_bf16_parts(L, O, m, C, groups):  # noqa: F811
+    gl, ol, g2o = _pair(L, O, _cloud(2550 + m, m, 0.7), 0.1)
+    rng = np.random.default_rng(m + C)
+    X = O.round_bf16(rng.normal(size=(ol.n, C)) + rng.normal(size=C))
+    W = O.round_bf16(rng.normal(size=(9, C, 24)) / np.sqrt(9 * C))
+    A = O.round_bf16(O.groupnorm(X.astype(np.float64), groups, eps=1e-5, relu=True)).astype(np.float64)
+    gW = _dev(np.ascontiguousarray(np.transpose(np.asarray(W, np.float32), (0, 2, 1))), torch.bfloat16)
+    got = gl.conv_preact(gl, _dev(np.asarray(X, np.float32)[g2o], torch.bfloat16), gW, groups=groups)
+    P.assert_close(P.rows_in_oracle_order(_host(got), g2o), O.round_bf16(ol.conv(ol, A, W.astype(np.float64))), P.TOL_BF16,
+                   f"m={m} C={C}")
+
+
 # first table by the cloud's size: worst case up to 16,384 points, half of it up to 65,536, then 2 slots per point, where a
 # sparse cloud overflows and is rebuilt (also when another stream asks first, and through coarse levels built before that)
 @pytest.mark.parametrize("m,sigma", [(16_384, 0.002), (16_385, 0.002), (65_536, 0.002), (70_000, 0.001)])

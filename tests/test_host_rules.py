@@ -1,0 +1,38 @@
+"""Host-side rules of the library that decide buffer sizes, checked without a
+GPU through the library's internal functions."""
+from __future__ import annotations
+
+import ctypes as C
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_1912_05905_amd import lattice
+    if not os.path.exists(lattice.LIB_PATH):
+        pytest.fail("liblattice.so is not built (run __graft_entry__.build())")
+    return lattice.lib()
+
+
+def _internal(lib, symbol, *args):
+    fn = getattr(lib, symbol)
+    fn.restype, fn.argtypes = C.c_int64, list(args)
+    return fn
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_group_norm_partials_fit_their_workspace(lib, bf16):
+    """Every width and row count around the points where the split changes: the partials that a launch of this dtype
+    writes (2 C doubles each) fit the workspace that its caller allocates."""
+    parts = _internal(lib, "_ZN3lat11gn_partialsElii", C.c_int64, C.c_int, C.c_int)
+    size = _internal(lib, "_ZN3lat18gn_workspace_bytesElii", C.c_int64, C.c_int, C.c_int)
+    for c in range(8 if bf16 else 4, 1025, 8 if bf16 else 4):
+        last = 0
+        for base in [*range(1, 400), *range(400, 300_000, 2048)]:
+            for n in (base - 1, base, base + 1):
+                p = parts(n, c, bf16)
+                assert p * 2 * c * 8 <= size(n, c, bf16), f"n={n} C={c}: {p} partials"
+                last = max(last, p)
+        assert 1 < last <= 2048
