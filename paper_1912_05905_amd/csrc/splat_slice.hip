@@ -841,7 +841,8 @@ __device__ inline void store_classes(float* __restrict__ out, int64_t p, int K, 
 // Every load is issued, from a valid address (a condition would make branches
 // of the loads, each waiting for all in flight): a vertex slot without a vertex
 // (a lattice the build flagged) reads row 0 with weight and coefficient 0,
-// channels past C the row's last ones, against zeros in wvec and Wc.
+// lanes past C the row's last channels, which are then replaced by zeros (a
+// product with a zero weight would make NaN of an infinite value).
 template <bool BF16, int LPR, int CPL, int NB>
 __global__ void __launch_bounds__(kBlock)
 k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
@@ -918,6 +919,14 @@ k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, in
       for (int q = 0; q < CPL; ++q)
 #pragma unroll
         for (int k = 0; k < 4; ++k) xn[q][k].widen(x[q][k]);
+      if (C < CW) {
+#pragma unroll
+        for (int q = 0; q < CPL; ++q)
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) x[q][k].v[i] = (cl + q * LPR) * EPL < C ? x[q][k].v[i] : 0.f;
+      }
       iv = iv_next;
       wq = wq_next;
       gather(iv);
@@ -1053,6 +1062,9 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
         } else {
           x[k] = *reinterpret_cast<const f32x4_v*>(static_cast<const float*>(vals) + at);
         }
+        // channels past C, which the last block may have: zeros, not the
+        // row's last channels
+        if (16 * cb + 16 > C && 16 * cb + 4 * lg >= C) x[k] = f32x4_v{0.f, 0.f, 0.f, 0.f};
       }
     };
     float part[4] = {0.f, 0.f, 0.f, 0.f};

@@ -123,6 +123,32 @@ def test_classifier_tiles(L, O, m, C, K, dtype):  # noqa: F811
     P.assert_close(_host(got), ref, P.TOL_F32, f"logits m={m} C={C} K={K} {dtype}")
 
 
+# infinite values in the last channels of a row that does not fill its lanes: the logits are infinite or NaN where the
+# formula makes them so and nowhere else (rows narrower and wider than the tiled form takes)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C", [24, 72, 136, 264])
+def test_classifier_infinite_values(L, O, C, dtype):  # noqa: F811
+    m, K = 300, 7
+    gl, ol, g2o = _pair(L, O, _cloud(2450 + C, m, 0.6), 0.1)
+    rng = np.random.default_rng(C)
+    X = rng.normal(size=(ol.n, C))
+    X = (O.round_bf16(X) if dtype == "bf16" else X).astype(np.float32)
+    idx, _ = ol.simplices()
+    X[idx[5, 0], C - 1] = -np.inf
+    X[idx[17, 2], C - 3] = -np.inf
+    X[idx[40, 1], C - 2] = np.inf
+    wv = (rng.normal(size=C) / np.sqrt(C)).astype(np.float32)
+    Wc = (rng.normal(size=(K, C)) / np.sqrt(C)).astype(np.float32)
+    with np.errstate(invalid="ignore"):
+        ref = ol.deform_slice_classify(X.astype(np.float64), wv.astype(np.float64), 0.1, Wc.astype(np.float64), None)
+    got = _host(gl.deform_slice_classify(_dev(X[g2o], torch.bfloat16 if dtype == "bf16" else None), _dev(wv), 0.1, _dev(Wc)))
+    assert np.isinf(ref).any(1).sum() > 2 and np.isfinite(ref).all(1).sum() > m // 2
+    for kind in (np.isposinf, np.isneginf, np.isnan):
+        assert np.array_equal(kind(got), kind(ref)), kind.__name__
+    ok = np.isfinite(ref)
+    P.assert_close(got[ok], ref[ok], P.TOL_F32, f"finite logits C={C} {dtype}")
+
+
 # GroupNorm statistics and their backward: rows around the 32-row parts and 8-row batches, one to 16 row slots
 @pytest.mark.parametrize("m,C,groups", [(2, 8, 2), (12, 64, 32), (40, 256, 32), (700, 128, 4), (1500, 1024, 32)])
 def test_group_norm_parts(L, O, m, C, groups):  # noqa: F811
