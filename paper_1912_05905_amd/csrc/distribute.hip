@@ -1028,7 +1028,9 @@ k_dist_fwd64(const int32_t* __restrict__ entries, const int32_t* __restrict__ en
         if ((starts >> i) & 1u) {
           emit();
           ckey = __builtin_amdgcn_readlane(v, i);
-          cmax = x;
+          // a piece that starts inside its list passes over NaN rows, as the
+          // walk down an uncut list does
+          cmax = ckey == key_before ? fmax(x, -static_cast<double>(INFINITY)) : x;
           crow = at;
         } else if (x > cmax) {
           cmax = x;

@@ -69,6 +69,55 @@ def test_distribute_backward_tiles(L, O, m, cf, widths, clump):  # noqa: F811
     _distribute_backward_case(L, O, gl, ol, g2o, pos, F, widths, m)
 
 
+# a maximum over a list cut by 128-entry ranges, some of its rows NaN: the walk passes over NaN rows behind the list's first
+# row, also where a range starts with one.  Two equal channels with an infinite gamma and weights +1 and -1 make NaN of the
+# rows where they are positive and leave the others finite.
+def test_distribute_backward_maximum_beside_nan(L, O):  # noqa: F811
+    rng = np.random.default_rng(3)
+    centres = np.stack(np.meshgrid(*[np.arange(3) * 4.0] * 3, indexing="ij"), -1).reshape(-1, 3) + [0.31, 0.42, 0.53]
+    pos = np.concatenate([c + 0.02 * rng.random((300, 3)) for c in centres]).astype(np.float32)
+    F = rng.normal(size=(len(pos), 4)).astype(np.float32)
+    gl, ol, g2o = _pair(L, O, pos, 1.0)
+    layers = [((rng.normal(size=(o, i)) / np.sqrt(i)).astype(np.float32), (0.1 * rng.normal(size=o)).astype(np.float32))
+              for i, o in ((7, 16), (16, 32), (32, 64))]
+    layers[1][0][1], layers[1][1][1] = layers[1][0][0], layers[1][1][0]
+    layers[2][0][:, 0], layers[2][0][:, 1] = 1.0, -1.0
+    gamma, beta = np.ones(7 + 16 + 32, np.float32), np.zeros(7 + 16 + 32, np.float32)
+    gamma[23:25] = np.inf
+    # the rows in float64; finite channels of the last layer's input and its outputs
+    idx, _ = ol.simplices()
+    v = idx.reshape(-1)
+    counts = np.bincount(v, minlength=ol.n)
+    g = np.repeat(pos.astype(np.float64), 4, 0)   # (sigma 1)
+    mu = np.stack([np.bincount(v, g[:, j], ol.n) / counts for j in range(3)], 1)
+    h = np.concatenate([g - mu[v], np.repeat(F.astype(np.float64), 4, 0)], 1)
+    for W, b in layers[:2]:
+        a = np.maximum((h - h.mean(0)) / np.sqrt(h.var(0) + 1e-5), 0.0)
+        h = a @ W.T.astype(np.float64) + b
+    xh = (h - h.mean(0)) / np.sqrt(h.var(0) + 1e-5)
+    a = np.maximum(xh, 0.0)
+    nan = xh[:, 0] > 0
+    out = a[:, 2:] @ layers[2][0][:, 2:].T.astype(np.float64) + layers[2][1]
+    dev = [(_dev(W), _dev(b)) for W, b in layers]
+    seen = 0
+    for u in np.nonzero(counts > 260)[0]:
+        D = np.zeros((ol.n, 64), np.float32)
+        D[u] = 1.0
+        got = gl.distribute_pointnet_backward(_dev(pos), _dev(F), dev, _dev(D[g2o]), (_dev(gamma), _dev(beta)))
+        dW3 = _host(got["dW3"])[:, 2:]
+        rows = np.nonzero(v == u)[0]
+        for c in range(64):
+            dist = np.abs(a[rows, 2:] - dW3[c]).max(1)
+            taken = rows[np.argmin(dist)]
+            assert dist.min() < 1e-4, (u, c)
+            if nan[taken]:
+                continue   # the list's first row is NaN and stays
+            finite = rows[~nan[rows]]
+            assert out[taken, c] >= out[finite, c].max() - 1e-9, (u, c, out[taken, c], out[finite, c].max())
+            seen += 1
+    assert seen > 100
+
+
 # convolution: rows and columns that do not fill a tile, channels that do not fill a stage, odd and even stage counts,
 # every tile of the dispatch that a small lattice reaches
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
