@@ -525,7 +525,7 @@ template <int KB, class Rows>
 __global__ void __launch_bounds__(kBlock)
 k_lin_wgrad(Rows rows, const float* __restrict__ f, int64_t ld_f, int K, int C, int64_t m, int64_t chunk,
             float* __restrict__ part) {
-  __shared__ float sum[KB * 16 * kLinCols];   // [j][c]
+  __shared__ __align__(16) float sum[KB * 16 * kLinCols];   // [j][c]
   __shared__ float sb[4][KB * 16];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int li = lane & 15, lg = lane >> 4;
