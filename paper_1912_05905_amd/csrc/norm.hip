@@ -17,6 +17,8 @@ constexpr int kBlock = 256;
 constexpr int kGnMaxParts = 2048;
 constexpr int kGnBatch = 8;      // rows a thread requests at once
 constexpr int kGnMinRows = 32;   // rows per workgroup on small levels
+constexpr int kGnParts = 512;    // partials up to which a workgroup takes fewer than kGnRows rows
+constexpr int kGnRows = 128;
 
 // Workgroup w sums rows [w * rows_per, (w + 1) * rows_per): thread t takes
 // the EPT channels EPT (t % groups_of_c) .. + EPT - 1 (16 bytes: 8 bf16 or 4
@@ -366,12 +368,19 @@ inline unsigned elementwise_grid(int64_t n, int C) {
 
 // Rows per partial: at least kGnMinRows (a level of a few thousand vertices
 // then fills most compute units; its few hundred partials are a few loads per
-// thread of the finalize), at most 2,048 partials on large ones.  With 128 rows
-// each and one row requested at a time, the statistics of 256 channels on 2.2k
-// and 5.8k vertices of a LiDAR scan took 11.0 and 10.6 us, and 4.8 us here.
+// thread of the finalize), at most kGnParts partials until a partial has
+// kGnRows rows, and at most kGnMaxParts on large levels.  With 128 rows each and
+// one row requested at a time, the statistics of 256 channels on 2.2k and 5.8k
+// vertices of a LiDAR scan took 11.0 and 10.6 us, and 4.8 us here.  The bound of
+// kGnParts is for levels between: with 32 rows each their 600 to 2,000 partials
+// cost the finalize more than the sums gain (64 bf16 channels on 52k vertices
+// with the convolution to 8 channels: 30 us with 128 rows, 37.5 with 32, 26 with
+// the bound; 256 channels 69, 79 and 57).
 void gn_parts(int64_t n, int C, int bf16, int64_t* nparts, int64_t* rows_per) {
   const int slots = kBlock / (C / (bf16 ? 8 : 4));
-  int64_t rp = std::max<int64_t>(std::max<int64_t>(slots, kGnMinRows), (n + kGnMaxParts - 1) / kGnMaxParts);
+  int64_t rp = std::max<int64_t>(slots, kGnMinRows);
+  rp = std::max<int64_t>(rp, std::min<int64_t>((n + kGnParts - 1) / kGnParts, kGnRows));
+  rp = std::max<int64_t>(rp, (n + kGnMaxParts - 1) / kGnMaxParts);
   rp = (rp + slots - 1) / slots * slots;
   *rows_per = rp;
   *nparts = std::max<int64_t>(1, (n + rp - 1) / rp);

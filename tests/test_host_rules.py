@@ -36,3 +36,16 @@ def test_group_norm_partials_fit_their_workspace(lib, bf16):
                 assert p * 2 * c * 8 <= size(n, c, bf16), f"n={n} C={c}: {p} partials"
                 last = max(last, p)
         assert 1 < last <= 2048
+
+
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_group_norm_partials_of_middle_levels(lib, bf16):
+    """Up to 65,536 rows a level has at most 512 partials (the finalize reads them all in one workgroup per group), beyond
+    that parts of at least 128 rows until there are 2,048 of them."""
+    parts = _internal(lib, "_ZN3lat11gn_partialsElii", C.c_int64, C.c_int, C.c_int)
+    for c in range(8, 1025, 8):
+        for n in (1, 31, 33, 5_000, 16_384, 16_385, 22_743, 52_353, 65_536):
+            assert parts(n, c, bf16) <= min(512, -(-n // 32)), (n, c)
+        for n in (65_537, 100_000, 262_144):
+            assert parts(n, c, bf16) <= -(-n // 128), (n, c)
+        assert parts(1_000_000, c, bf16) <= 2048
