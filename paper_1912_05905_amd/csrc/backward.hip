@@ -361,9 +361,13 @@ inline unsigned blocks_for(int64_t threads) { return static_cast<unsigned>((thre
 // over taps and tiles (more chunks would only grow the partials the reduction
 // reads), in multiples of 8 so that the taps of a chunk, which gather the same
 // rows, run on one XCD (workgroup b runs on XCD b % 8), and at least 64
-// vertices each.
+// vertices each.  From three tiles on, a chunk's partials (150 KB a tile) cost
+// more than small chunks gain, and more than 8 chunks have at least 256
+// vertices: 128 x 128 fp32 on 1.3k and 3.1k vertices 18.5 and 24.5 us with 64,
+// 12.7 and 20.8 here; with 8 chunks 256 x 256 on 1.3k takes 29.7, with 6 31.5.
 void wgrad_chunks(int64_t n_out, int tiles, int64_t* chunks, int64_t* V) {
   int64_t want = std::max<int64_t>(8, (kWgTargetBlocks / (9 * static_cast<int64_t>(tiles)) + 7) / 8 * 8);
+  if (tiles >= 3) want = std::min<int64_t>(want, std::max<int64_t>(8, (n_out + 255) / 256));
   want = std::min<int64_t>(want, (n_out + 63) / 64);
   int64_t v = (n_out + want - 1) / want;
   v = (v + 63) / 64 * 64;

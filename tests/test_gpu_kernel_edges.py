@@ -34,7 +34,8 @@ def test_linear_backward_tiles(L, O, m, C, K):  # noqa: F811
 
 # weight gradient: 64 x 64 tiles, steps of 16 (fp32) and 32 (bf16) vertices, chunks of 64, missing taps
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("m,cin,cout", [(1, 8, 8), (9, 64, 72), (65, 56, 64), (700, 136, 128), (3000, 24, 200)])
+@pytest.mark.parametrize("m,cin,cout", [(1, 8, 8), (9, 64, 72), (65, 56, 64), (700, 136, 128), (700, 64, 192),
+                                        (3000, 24, 200)])
 def test_weight_gradient_tiles(L, O, m, cin, cout, dtype):  # noqa: F811
     gl, ol, g2o = _pair(L, O, _cloud(2100 + m, m, 0.7), 0.07)
     gc, oc = gl.coarsen(), ol.coarsen()

@@ -49,3 +49,19 @@ def test_group_norm_partials_of_middle_levels(lib, bf16):
         for n in (65_537, 100_000, 262_144):
             assert parts(n, c, bf16) <= -(-n // 128), (n, c)
         assert parts(1_000_000, c, bf16) <= 2048
+
+
+def test_weight_gradient_chunks(lib):
+    """Partials of the weight gradient: one set of 9 Cout Cin + Cout sums per vertex chunk.  Small levels have chunks of at
+    least 64 vertices, from three 64 x 64 tiles on of 256 beyond 8 chunks, large ones three workgroups per compute unit."""
+    floats = _internal(lib, "_ZN3lat20wgrad_partial_floatsElii", C.c_int64, C.c_int, C.c_int)
+    assert floats(0, 64, 64) == 0
+    for n in (1, 63, 64, 65, 1284, 2048, 3102, 8445, 200_000, 4_000_000):
+        for cout, cin in ((4, 4), (64, 64), (72, 40), (192, 64), (128, 128), (256, 256), (512, 512), (1024, 1024)):
+            tiles = -(-cout // 64) * -(-cin // 64)
+            per = 9 * cout * cin + cout
+            chunks, rest = divmod(floats(n, cout, cin), per)
+            assert rest == 0 and 1 <= chunks <= max(1, -(-n // 64)), (n, cout, cin)
+            assert chunks <= max(8, 768 // (9 * tiles) + 8)
+            if tiles >= 3:
+                assert chunks <= max(8, -(-n // 256)), (n, cout, cin, chunks)
