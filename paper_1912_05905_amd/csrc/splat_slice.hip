@@ -841,8 +841,10 @@ __device__ inline void store_classes(float* __restrict__ out, int64_t p, int K, 
 // Every load is issued, from a valid address (a condition would make branches
 // of the loads, each waiting for all in flight): a vertex slot without a vertex
 // (a lattice the build flagged) reads row 0 with weight and coefficient 0,
-// lanes past C the row's last channels, which are then replaced by zeros (a
-// product with a zero weight would make NaN of an infinite value).
+// lanes past C zeros in place of a row (the row's last channels against zeros in
+// wvec and Wc would make NaN of an infinite value, and selects on the loaded
+// values took 9% at 160 to 224 fp32 channels).
+__device__ const uint4 kNoChannels = {0u, 0u, 0u, 0u};
 template <bool BF16, int LPR, int CPL, int NB>
 __global__ void __launch_bounds__(kBlock)
 k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
@@ -895,14 +897,22 @@ k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, in
     return min(tile * TP + static_cast<int64_t>(step % STEPS) * PPS + pl, m - 1);
   };
   Raw<BF16> xn[CPL][4];
+  // the lane's channels of row 0, and the rows' distance (0 where the lane is past C)
+  const void* base[CPL];
+  int64_t ld[CPL];
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {
+    const int ch = (cl + q * LPR) * EPL;
+    const bool on = (!BF16 && LPR == 8 && CPL == 2) || ch < C;   // (two chunks a lane: 64 channels, all lanes)
+    base[q] = on ? static_cast<const char*>(vals) + ch * (BF16 ? 2 : 4) : static_cast<const void*>(&kNoChannels);
+    ld[q] = on ? ld_vals : 0;
+  }
   auto gather = [&](const int4& v) {
     const int32_t vi[4] = {max(v.x, 0), max(v.y, 0), max(v.z, 0), max(v.w, 0)};
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      const int ch = min((cl + q * LPR) * EPL, C - EPL);
+    for (int q = 0; q < CPL; ++q)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) xn[q][k].load(vals, static_cast<int64_t>(vi[k]) * ld_vals + ch);
-    }
+      for (int k = 0; k < 4; ++k) xn[q][k].load(base[q], static_cast<int64_t>(vi[k]) * ld[q]);
   };
   int4 iv = idx[point(0)], iv_next = idx[point(1)];
   float4 wq = w[point(0)], wq_next = w[point(1)];
@@ -919,14 +929,6 @@ k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, in
       for (int q = 0; q < CPL; ++q)
 #pragma unroll
         for (int k = 0; k < 4; ++k) xn[q][k].widen(x[q][k]);
-      if (C < CW) {
-#pragma unroll
-        for (int q = 0; q < CPL; ++q)
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) x[q][k].v[i] = (cl + q * LPR) * EPL < C ? x[q][k].v[i] : 0.f;
-      }
       iv = iv_next;
       wq = wq_next;
       gather(iv);
@@ -1050,8 +1052,13 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
     const int32_t vi[4] = {max(iv.x, 0), max(iv.y, 0), max(iv.z, 0), max(iv.w, 0)};
     const bool have[4] = {iv.x >= 0, iv.y >= 0, iv.z >= 0, iv.w >= 0};
     const float bw[4] = {have[0] ? wq.x : 0.f, have[1] ? wq.y : 0.f, have[2] ? wq.z : 0.f, have[3] ? wq.w : 0.f};
-    auto gather = [&](int cb, f32x4_v (&x)[4]) {
-      const int ch = min(16 * cb + 4 * lg, C - 4);
+    // TAIL: the last block of channels where it is not full: lanes past C hold
+    // zeros, not the row's last channels.  (Apart from the others: a select in
+    // the loop keeps the compiler from overlapping its loads, 35 and 57 us at
+    // 512 fp32 channels of 8,000 points.)
+    auto gather = [&](int cb, f32x4_v (&x)[4], auto tail_c) {
+      constexpr bool TAIL = decltype(tail_c)::value;
+      const int c = 16 * cb + 4 * lg, ch = TAIL ? min(c, C - 4) : c;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int64_t at = static_cast<int64_t>(vi[k]) * ld_vals + ch;
@@ -1062,15 +1069,14 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
         } else {
           x[k] = *reinterpret_cast<const f32x4_v*>(static_cast<const float*>(vals) + at);
         }
-        // channels past C, which the last block may have: zeros, not the
-        // row's last channels
-        if (16 * cb + 16 > C && 16 * cb + 4 * lg >= C) x[k] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+        if (TAIL && c >= C) x[k] = f32x4_v{0.f, 0.f, 0.f, 0.f};
       }
     };
+    const int full = C / 16;
     float part[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int cb = 0; cb < blocks; ++cb) {
+    auto offsets = [&](int cb, auto tail_c) {
       f32x4_v x[4];
-      gather(cb, x);
+      gather(cb, x, tail_c);
       const f32x4_v wv = *reinterpret_cast<const f32x4_v*>(wvl + 16 * cb + 4 * lg);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -1084,7 +1090,9 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
 #pragma unroll
         for (int k = 0; k < 4; ++k) part[k] += (qk[k] - mx) * wv[e];
       }
-    }
+    };
+    for (int cb = 0; cb < full; ++cb) offsets(cb, std::false_type{});
+    if (full < blocks) offsets(full, std::true_type{});
     float coef[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -1094,16 +1102,20 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
     }
     ClassSums<NB> sums;
     const f32x4_v* wf = reinterpret_cast<const f32x4_v*>(wl) + lane;
-    for (int cb = 0; cb < blocks; ++cb) {
+    auto classes = [&](int cb, auto tail_c) {
       f32x4_v x[4], wr[NB];
-      gather(cb, x);
+      gather(cb, x, tail_c);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) wr[nb] = wf[(cb * NB + nb) * 64];
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         sums.add(wr, e, coef[0] * x[0][e] + coef[1] * x[1][e] + coef[2] * x[2][e] + coef[3] * x[3][e]);
+    };
+    for (int cb = 0; cb < full; ++cb) {
+      classes(cb, std::false_type{});
       if (cb % kClassifyRun == kClassifyRun - 1) sums.flush();
     }
+    if (full < blocks) classes(full, std::true_type{});
     sums.flush();
     f32x4_v acc[NB];
 #pragma unroll

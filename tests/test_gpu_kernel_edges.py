@@ -176,9 +176,9 @@ def test_classifier_tiles(L, O, m, C, K, dtype):  # noqa: F811
 # infinite values in the last channels of a row that does not fill its lanes: the logits are infinite or NaN where the
 # formula makes them so and nowhere else (rows narrower and wider than the tiled form takes)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("C", [24, 72, 136, 264])
-def test_classifier_infinite_values(L, O, C, dtype):  # noqa: F811
-    m, K = 300, 7
+@pytest.mark.parametrize("m,C,K", [(300, 24, 7), (300, 72, 7), (300, 72, 40), (300, 136, 7), (2100, 136, 40), (300, 264, 7),
+                                   (2100, 264, 21)])
+def test_classifier_infinite_values(L, O, m, C, K, dtype):  # noqa: F811
     gl, ol, g2o = _pair(L, O, _cloud(2450 + C, m, 0.6), 0.1)
     rng = np.random.default_rng(C)
     X = rng.normal(size=(ol.n, C))
