@@ -1124,6 +1124,138 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
   }
 }
 
+// The same by lane groups: a point's row is formed in the registers of LPR lanes
+// as in k_deform_slice and multiplied by Wc (K x C in LDS) there; the KP >= K
+// logit partials of a lane group are summed by a reduce-scatter, after which
+// each lane holds KP / LPR finished classes (the block its exchange bits
+// name).  It spreads a small cloud over the chip, where the 16 points of a wave
+// above are a chain of dependent steps, and it has no work for padded channels
+// and classes (classify_by_rows has the figures).
+// One exchange of the reduce-scatter: lanes whose bit OFF is set keep the upper
+// LEN values, the others the lower LEN, and each adds the half its partner
+// gives away; blk gathers the kept halves' bits.
+template <int OFF, int LEN, int KP>
+__device__ inline void reduce_scatter_step(float (&lg)[KP], int lane, int& blk) {
+  const bool up = (lane & OFF) != 0;
+#pragma unroll
+  for (int i = 0; i < LEN; ++i) {
+    const float give = up ? lg[i] : lg[i + LEN];
+    const float keep = up ? lg[i + LEN] : lg[i];
+    lg[i] = keep + xor_lane<OFF>(give);
+  }
+  blk = 2 * blk + (up ? 1 : 0);
+}
+
+template <bool BF16, int LPR, int CPL, int KP>
+__global__ void __launch_bounds__(kBlock)
+k_deform_classify_rows(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
+                       const void* __restrict__ vals, int64_t ld_vals, int C, const float* __restrict__ wvec, float beta,
+                       const float* __restrict__ Wc, const float* __restrict__ bc, int K, float* __restrict__ out,
+                       unsigned nblk) {
+  using Ch = Chunk<BF16>;
+  extern __shared__ __align__(16) float wl[];   // [K][C]
+  for (int i = threadIdx.x; i < K * C; i += kBlock) wl[i] = Wc[i];
+  __syncthreads();
+  const int lane = threadIdx.x & (LPR - 1);
+  const int nchunk = C / Ch::N;
+  // The weights are staged once per workgroup, which then walks a
+  // contiguous range of the nblk logical blocks (each XCD a contiguous
+  // share of the ranges, as xcd_item).
+  const unsigned G = gridDim.x;   // a multiple of 8
+  const unsigned r = (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8;
+  const unsigned per = (nblk + G - 1) / G;
+  const unsigned lb1 = min((r + 1) * per, nblk);
+  for (unsigned lb = r * per; lb < lb1; ++lb) {
+    const int64_t p = (static_cast<int64_t>(lb) * kBlock + threadIdx.x) / LPR;
+    const bool live = p < m;
+    int4 iv = make_int4(-1, -1, -1, -1);
+    float4 wq = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (live) { iv = idx[p]; wq = w[p]; }
+    const int32_t vi[4] = {iv.x, iv.y, iv.z, iv.w};
+    const float bw[4] = {wq.x, wq.y, wq.z, wq.w};
+    float x[CPL][4][Ch::N];
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      const int ch = lane + q * LPR;
+      const bool on = live && ch < nchunk;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (on && vi[k] >= 0) {
+          Ch c;
+          c.load(vals, static_cast<int64_t>(vi[k]) * ld_vals + static_cast<int64_t>(ch) * Ch::N);
+#pragma unroll
+          for (int i = 0; i < Ch::N; ++i) x[q][k][i] = c.v[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < Ch::N; ++i) x[q][k][i] = 0.f;
+        }
+      }
+      if (on) {
+#pragma unroll
+        for (int i = 0; i < Ch::N; ++i) {
+          const float wc = wvec[ch * Ch::N + i];
+          float qk[4];
+          float mx = -INFINITY;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            qk[k] = bw[k] * x[q][k][i];
+            mx = fmaxf(mx, qk[k]);
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) part[k] += (qk[k] - mx) * wc;
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) part[k] = group_sum<LPR>(part[k]);
+    float coef[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) coef[k] = bw[k] + tanhf(beta + part[k]);
+    float lg[KP];
+#pragma unroll
+    for (int j = 0; j < KP; ++j) lg[j] = 0.f;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      const int ch = lane + q * LPR;
+      if (!(live && ch < nchunk)) continue;
+#pragma unroll
+      for (int i = 0; i < Ch::N; i += 4) {
+        float f[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          f[u] = coef[0] * x[q][0][i + u] + coef[1] * x[q][1][i + u] + coef[2] * x[q][2][i + u] +
+                 coef[3] * x[q][3][i + u];
+#pragma unroll
+        for (int j = 0; j < KP; ++j) {
+          if (j >= K) break;
+          const float4 wv4 = *reinterpret_cast<const float4*>(wl + j * C + ch * Ch::N + i);
+          lg[j] += wv4.x * f[0] + wv4.y * f[1] + wv4.z * f[2] + wv4.w * f[3];
+        }
+      }
+    }
+    // the exchanges in the order of their cost (cheap ones move the most
+    // values); blk = the class block this lane keeps
+    int blk = 0;
+    constexpr int S = (LPR >= 2) + (LPR >= 4) + (LPR >= 8) + (LPR >= 16) + (LPR >= 32) + (LPR >= 64);
+    static_assert((KP >> S) >= 1, "at least one class per lane");
+    if constexpr (LPR >= 2) reduce_scatter_step<1, (KP >> 1)>(lg, lane, blk);
+    if constexpr (LPR >= 4) reduce_scatter_step<2, (KP >> 2)>(lg, lane, blk);
+    if constexpr (LPR >= 16) reduce_scatter_step<8, (KP >> 3)>(lg, lane, blk);
+    if constexpr (LPR >= 8) reduce_scatter_step<4, (KP >> (LPR >= 16 ? 4 : 3))>(lg, lane, blk);
+    if constexpr (LPR >= 32) reduce_scatter_step<16, (KP >> 5)>(lg, lane, blk);
+    if constexpr (LPR >= 64) reduce_scatter_step<32, (KP >> 6)>(lg, lane, blk);
+    if (live) {
+      constexpr int OWN = KP / LPR;
+#pragma unroll
+      for (int i = 0; i < OWN; ++i) {
+        const int j = blk * OWN + i;
+        if (j < K) out[p * K + j] = lg[i] + (bc ? bc[j] : 0.f);
+      }
+    }
+  }
+}
+
 // DeformSlice backward, per point (C channels over LPR lanes, CPL 16-byte
 // chunks per lane, as in the forward), with g = dL/dout_p:
 //   q_k = b_k x_k; am_c = the first slot k whose float32 q_k is maximal,
@@ -1484,6 +1616,67 @@ void classify_launch(Kernel kernel, bool* limit_set, size_t lds, int points_per_
          out, vec_out, nblk);
 }
 
+// Whether the classifier runs by lane groups (k_deform_classify_rows) rather
+// than on the matrix cores.  Lines from sweeps over 250 to 200,000 points, 16 to
+// 512 channels and 3 to 50 classes (us by lane groups and on the matrix cores):
+// the latter take 3 to 50 us however few the points are, the time of the former
+// grows with points, channels and classes.
+//   48 fp32 channels, 5 classes: 3.9 and 5.4 at 2,000 points, 6.2 and 6.8 at 24,000, 12 and 8.4 at 40,000
+//   64 fp32, 3 classes: 4.5 and 5.0 at 2,000, 5.6 and 6.0 at 24,000, 8.3 and 7.5 at 40,000; 10: 5.4 and 5.0 at 2,000
+//   128 fp32, 20 classes: 5.5 and 11 at 2,000, 7.8 and 11 at 8,000, 20.7 and 13.8 at 24,000
+//   128 bf16, 5 classes: 5.0 and 7.5 at 2,000, 9.5 and 10.4 at 24,000; 20: 7.4 and 9.6, 17.9 and 13.1
+//   224 fp32, 20 classes: 13.2 and 19.1 at 1,000, 23.5 and 19.2 at 2,000
+//   160 bf16, 5 classes: 5.1 and 11.4 at 1,000, 10.5 and 11.8 at 12,000, 27.5 and 31.8 at 40,000, 109 and 156 at
+//   200,000 (its tiles are padded to 256 channels and 16 classes); 20: 13.2 and 15.4 at 8,000, 39.8 and 29.3 at 24,000
+//   512 fp32, 20 classes: 31.6 and 43.1 at 2,000, 47.9 and 37.9 at 4,000
+bool classify_by_rows(int64_t m, int C, int K, bool bf16) {
+  if (C <= 32) return false;
+  if (C <= 64 && (bf16 || C == 64)) return K <= 4 && m <= (bf16 ? 40000 : 32768);
+  if (C <= 64) return K <= 32 && m * (K + 8) <= 360000;
+  if (C <= 128 && bf16) return K <= 32 && m * (K + 2) <= 185000;
+  if (C <= 128) return K <= 32 ? m * (K + 32) <= 560000 : m <= 1500;
+  if (C <= 256 && bf16)
+    return K <= 3 || (K <= 32 ? m * (K + 10) * C <= 46000000 : m <= 2000) ||
+           (K * C <= 1920 && m >= (K * C <= 1000 ? 18000 : 100000));
+  if (C <= 256) return m <= 1500;
+  return m <= (K <= 20 ? (bf16 ? 14 : 13) * C / 2 : (bf16 ? 2100 : 1800));
+}
+
+template <bool BF16, int LPR, int CPL, int KP>
+void classify_rows_launch(const int32_t* idx, const float* w, int64_t m, const void* vals, int64_t ldv, int C,
+                          const float* wv, float beta, const float* Wc, const float* bc, int K, float* out,
+                          hipStream_t s) {
+  static bool set = false;
+  if (!set) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_deform_classify_rows<BF16, LPR, CPL, KP>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kClassifyMaxWeights);
+    set = true;
+  }
+  const unsigned nblk = grid_for(m, LPR);
+  launch((k_deform_classify_rows<BF16, LPR, CPL, KP>), dim3(std::min(xcd_grid(nblk), kClassifyGrid)), dim3(kBlock),
+         static_cast<uint32_t>(4 * K * C), s, reinterpret_cast<const int4*>(idx), reinterpret_cast<const float4*>(w), m,
+         vals, ldv, C, wv, beta, Wc, bc, K, out, nblk);
+}
+
+// the lane groups of the widths and class counts that classify_by_rows takes
+template <bool BF16>
+void classify_rows_dispatch(const int32_t* idx, const float* w, int64_t m, const void* vals, int64_t ldv, int C,
+                            const float* wv, float beta, const float* Wc, const float* bc, int K, float* out,
+                            hipStream_t s) {
+  auto go = [&](auto kernel) { kernel(idx, w, m, vals, ldv, C, wv, beta, Wc, bc, K, out, s); };
+  const bool two = C / Chunk<BF16>::N > 64;   // two chunks per lane of a wave
+  if constexpr (BF16) {
+    if (C <= 64) return go(classify_rows_launch<true, 8, 1, 32>);
+    if (C <= 128) return go(classify_rows_launch<true, 16, 1, 32>);
+    if (C <= 256) return K <= 32 ? go(classify_rows_launch<true, 32, 1, 32>) : go(classify_rows_launch<true, 32, 1, 64>);
+  } else {
+    if (C < 64) return go(classify_rows_launch<false, 16, 1, 32>);
+    if (C == 64) return go(classify_rows_launch<false, 8, 2, 32>);
+    if (C <= 128) return K <= 32 ? go(classify_rows_launch<false, 32, 1, 32>) : go(classify_rows_launch<false, 32, 1, 64>);
+  }
+  return two ? go(classify_rows_launch<BF16, 64, 2, 64>) : go(classify_rows_launch<BF16, 64, 1, 64>);
+}
+
 template <bool BF16, int NB>
 void deform_classify_dispatch(const int32_t* idx, const float* w, int64_t m, const void* vals, int64_t ldv, int C,
                               const float* wv, float beta, const float* Wc, const float* bc, int K, float* out,
@@ -1517,6 +1710,11 @@ void launch_deform_classify(const int32_t* idx, const float* w, int64_t m, const
                             hipStream_t s) {
   if (m <= 0) return;
   ScopedKernelTimer tm("deform_slice", s);
+  if (classify_by_rows(m, C, K, bf16 != 0)) {
+    if (bf16) classify_rows_dispatch<true>(idx, w, m, vals, ld_vals, C, wv, beta, Wc, bc, K, out, s);
+    else classify_rows_dispatch<false>(idx, w, m, vals, ld_vals, C, wv, beta, Wc, bc, K, out, s);
+    return;
+  }
   const int nb = (K + 15) / 16;   // K <= 64
 #define DCL_GO(BFV, NBV) return deform_classify_dispatch<BFV, NBV>(idx, w, m, vals, ld_vals, C, wv, beta, Wc, bc, K, out, s)
 #define DCL_NB(BFV)              \

@@ -154,10 +154,13 @@ def test_conv_tiles(L, O, m, cin, cout, pre, dtype):  # noqa: F811
         P.assert_close(P.rows_in_oracle_order(_host(got), pd), rnd(ref), tol, f"m={m} {cin}->{cout} {dtype} pre={pre} up={up}")
 
 
-# DeformSlice + classifier: 16-point tiles of 1 to 64 lanes per row, 16-class blocks, wide rows, unaligned class counts
+# DeformSlice + classifier: 16-point tiles of 1 to 64 lanes per row, 16-class blocks, wide rows, unaligned class counts; by
+# lane groups on small clouds (32 or 64 classes kept, one or two chunks a lane) and with few bf16 classes on large ones
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("m,C,K", [(1, 8, 1), (15, 16, 17), (65, 40, 16), (257, 72, 5), (300, 136, 33), (100, 256, 64),
-                                   (70, 264, 60), (33, 504, 32)])
+                                   (70, 264, 60), (33, 504, 32), (90, 64, 4), (91, 64, 5), (260, 72, 33), (261, 128, 40),
+                                   (700, 40, 32), (15_001, 40, 32), (1701, 136, 50), (2001, 256, 40), (1801, 264, 60), (3700, 512, 7),
+                                   (2002, 504, 32), (30_001, 104, 9), (100_000, 160, 12), (18_001, 200, 5), (9001, 192, 3)])
 def test_classifier_tiles(L, O, m, C, K, dtype):  # noqa: F811
     gl, ol, g2o = _pair(L, O, _cloud(2400 + m, m, 0.6), 0.1)
     rng = np.random.default_rng(m)
@@ -174,7 +177,7 @@ def test_classifier_tiles(L, O, m, C, K, dtype):  # noqa: F811
 
 
 # infinite values in the last channels of a row that does not fill its lanes: the logits are infinite or NaN where the
-# formula makes them so and nowhere else (rows narrower and wider than the tiled form takes)
+# formula makes them so and nowhere else (tiled form, wide rows, lane groups)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("m,C,K", [(300, 24, 7), (300, 72, 7), (300, 72, 40), (300, 136, 7), (2100, 136, 40), (300, 264, 7),
                                    (2100, 264, 21)])
