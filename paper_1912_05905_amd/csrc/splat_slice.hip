@@ -15,6 +15,8 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int64_t kDeformBwdGrid = 1024;   // workgroups of the DeformSlice backward's per-point pass
 constexpr unsigned kClassifyGrid = 2048;   // workgroups of the fused classifier (a multiple of 8)
+constexpr int64_t kSliceWideM = 4096;         // points beyond which rows wider than 128 channels are sliced by a wave,
+constexpr int64_t kSliceWideM128 = 131072;    // and bf16 rows of 65 to 128 channels
 constexpr int kClassifyMaxWeights = 16384; // K x C classifier weights staged in LDS
 constexpr int kClassifyTileC = 256;        // widest rows whose LDS tiles leave room for the weights
 constexpr int kClassifyMaxLds = 160 * 1024;
@@ -127,6 +129,19 @@ template <> struct Chunk<true> {
     for (int i = 0; i < 4; ++i)
       w[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
     *reinterpret_cast<uint4*>(static_cast<uint16_t*>(base) + elem) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+};
+
+// 4 bf16 channels, for lanes that store a whole 16 bytes of fp32 each.
+struct HalfChunk {
+  static constexpr int N = 4;
+  float v[N];
+  __device__ inline void load(const void* base, int64_t elem) {
+    const uint2 u = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(base) + elem);
+    v[0] = __uint_as_float(u.x << 16);
+    v[1] = __uint_as_float(u.x & 0xffff0000u);
+    v[2] = __uint_as_float(u.y << 16);
+    v[3] = __uint_as_float(u.y & 0xffff0000u);
   }
 };
 
@@ -540,12 +555,12 @@ k_splat_finish(const int32_t* __restrict__ offsets, const int32_t* __restrict__ 
 // without branches.
 // SCALED: every vertex row is taken times vscale[vertex], which is folded into
 // the weights (the gradient of a normalised splat).
-template <bool BF16, int LPR, bool SCALED>
+// Ch: a lane's channels of a row.
+template <class Ch, int LPR, bool SCALED>
 __global__ void __launch_bounds__(kBlock)
 k_slice(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
         const void* __restrict__ vals, int64_t ld_vals, int C, float* __restrict__ out,
         const float* __restrict__ vscale, unsigned nblk) {
-  using Ch = Chunk<BF16>;
   constexpr int PP = 2;
   const int lane = threadIdx.x & (LPR - 1);
   const int64_t p0 = PP * xcd_item<LPR>(nblk);
@@ -593,17 +608,24 @@ k_slice(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
   }
 }
 
-// Slice of rows wider than 64 channels: a wave takes whole points, PP
-// consecutive ones, a lane V consecutive channels of each.  Indices, weights
-// and row addresses are then the same for the wave and are read and computed
-// by the scalar unit.  What bounds the slice of wide rows is the sum of its
-// vector operations, its gathers through the L1 (195 us alone for 1M points of
-// 256 bf16 channels) and its stores (220 us alone); this takes the addresses
-// and the weights' selects off the vector unit and stores whole lines: 380 us with lane groups, 342
-// here (128 channels of 200k points: 44 and 40).  More points a wave, a loop
-// over points and other orders of the blocks made no difference.
-// Up to 64 channels a wave would have less than 4 bytes a lane to load, and
-// the lane groups of k_slice stay.
+// Slice of wide rows: a wave takes whole points, PP consecutive ones, a lane V
+// consecutive channels of each.  Indices, weights and row addresses are then the
+// same for the wave and are read and computed by the scalar unit.  What bounds
+// the slice of wide rows is the sum of its vector operations, its gathers through
+// the L1 (195 us alone for 1M points of 256 bf16 channels) and its stores (220 us
+// alone); this takes the addresses and the weights' selects off the vector unit
+// and stores whole lines: 446 us with lane groups, 361 here.  More points a
+// wave, a loop over points and other orders of the blocks made no difference.
+// Lane groups (k_slice) take
+//   fp32 rows up to 128 channels, whose 16-byte stores a wave would halve (128
+//     channels of 120k points: 15 us, a wave per point 20; 72 channels of 1M: 189
+//     and 219; 136 channels of 120k: 25 and 20);
+//   bf16 rows of 65 to 128 channels up to kSliceWideM128 points, 4 channels a
+//     lane (120k points of 128 channels: 14.5 us, a wave per point 18, 8 channels
+//     a lane 27; 200k points 46, 42 and 48, but 25, 29 and 26 with rows that the
+//     caches hold);
+//   clouds up to kSliceWideM points, which would have too few waves (1,024
+//     channels of 2,000 points: 4.8 us and 6.2).
 template <bool BF16, int V, bool SCALED>
 __global__ void __launch_bounds__(kBlock)
 k_slice_wide(const int4* __restrict__ idx, const float4* __restrict__ w, int64_t m,
@@ -1518,21 +1540,27 @@ void slice_dispatch(int lpr, const int32_t* idx, const float* w, int64_t m, cons
   const int4* i4 = reinterpret_cast<const int4*>(idx);
   const float4* w4 = reinterpret_cast<const float4*>(w);
   const dim3 b(kBlock);
-  if (C > 64) {   // a wave per point
+  auto go = [&](auto kernel, int lanes) {
+    const unsigned nblk = grid_for((m + 1) / 2, lanes);   // two points per lane group
+    launch(kernel, dim3(xcd_grid(nblk)), b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk);
+  };
+  auto wide = [&](auto kernel) {   // a wave per point
     const int64_t per_block = (kBlock / 64) * (BF16 ? 4 : 2);
     const unsigned nblk = static_cast<unsigned>((m + per_block - 1) / per_block);
-    const auto kernel = C > 128 ? k_slice_wide<BF16, 4, SCALED> : k_slice_wide<BF16, 2, SCALED>;
     launch(kernel, dim3(xcd_grid(nblk)), b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk);
-    return;
-  }
-  const unsigned nblk = grid_for((m + 1) / 2, lpr);   // two points per lane group
-  const dim3 g(xcd_grid(nblk));
+  };
+  if (C > 128 && m > kSliceWideM) return wide(k_slice_wide<BF16, 4, SCALED>);
+  if constexpr (BF16)
+    if (C > 64 && C <= 128)
+      return m > kSliceWideM128 ? wide(k_slice_wide<true, 2, SCALED>) : go(k_slice<HalfChunk, 32, SCALED>, 32);
   switch (lpr) {
-    case 1: launch((k_slice<BF16, 1, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
-    case 2: launch((k_slice<BF16, 2, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
-    case 4: launch((k_slice<BF16, 4, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
-    case 8: launch((k_slice<BF16, 8, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;
-    default: launch((k_slice<BF16, 16, SCALED>), g, b, 0, s, i4, w4, m, vals, ldv, C, out, vscale, nblk); break;   // C <= 64
+    case 1: return go(k_slice<Chunk<BF16>, 1, SCALED>, 1);
+    case 2: return go(k_slice<Chunk<BF16>, 2, SCALED>, 2);
+    case 4: return go(k_slice<Chunk<BF16>, 4, SCALED>, 4);
+    case 8: return go(k_slice<Chunk<BF16>, 8, SCALED>, 8);
+    case 16: return go(k_slice<Chunk<BF16>, 16, SCALED>, 16);
+    case 32: return go(k_slice<Chunk<BF16>, 32, SCALED>, 32);
+    default: return go(k_slice<Chunk<BF16>, 64, SCALED>, 64);
   }
 }
 

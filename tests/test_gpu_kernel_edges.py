@@ -273,9 +273,11 @@ def test_hinted_table_nearly_full(L, O):  # noqa: F811
     gl.destroy()
 
 
-# slice: lane groups up to 64 channels; beyond, a wave per point with 2 or 4 channels a lane, several passes over a row
+# slice: lane groups up to 128 channels and on small clouds; a wave per point with 4 channels a lane on rows beyond 128
+# channels and with 2 on large clouds of 65 to 128 bf16 channels, several passes over a row
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("m,C", [(1, 8), (3, 64), (5, 72), (258, 128), (259, 136), (1023, 264), (77, 1032)])
+@pytest.mark.parametrize("m,C", [(1, 8), (3, 64), (5, 72), (258, 128), (259, 136), (1023, 264), (77, 1032), (4096, 136),
+                                 (4097, 136), (4099, 264), (4101, 1032), (131_073, 72), (131_079, 128)])
 def test_slice_tiles(L, O, m, C, dtype):  # noqa: F811
     gl, ol, g2o = _pair(L, O, _cloud(2700 + m, m, 0.6), 0.1)
     X = np.random.default_rng(m).normal(size=(ol.n, C))
@@ -286,7 +288,8 @@ def test_slice_tiles(L, O, m, C, dtype):  # noqa: F811
 
 # gradient of a normalised splat: 1 / (weight sum), given or summed, folded into the slice's weights; lane groups and wave form
 @pytest.mark.parametrize("given", [True, False])
-@pytest.mark.parametrize("m,C", [(1, 4), (3, 8), (17, 16), (65, 64), (258, 68), (259, 128), (515, 132), (77, 516)])
+@pytest.mark.parametrize("m,C", [(1, 4), (3, 8), (17, 16), (65, 64), (258, 68), (259, 128), (515, 132), (77, 516),
+                                 (4097, 132), (4099, 516)])
 def test_splat_backward_scales(L, O, m, C, given):  # noqa: F811
     gl, ol, g2o = _pair(L, O, _cloud(2800 + m, m, 0.6), 0.1)
     dX = np.random.default_rng(m + C).normal(size=(ol.n, C)).astype(np.float32)
