@@ -524,9 +524,14 @@ int prepare_build(lattice_s* L, const lattice_s* parent, int64_t cap, hipStream_
 // A table that can be rebuilt larger counts as overflowed once a key finds no
 // slot within this many probes.  Linear probing of a table that fills up takes
 // time that grows with its size (a room of 65,536 points with 142k vertices in
-// 131,072 slots: 428 ms, nearly all of it in the insert), a rebuild about 2 ms.
-// At the loads a table is sized for, up to about 0.8, no probe sequence gets
-// this long.
+// 131,072 slots: 428 ms, nearly all of it in the insert); with the bound, and no
+// convolution tables for a level that overflowed, clouds of 30,000, 70,000 and
+// 150,000 points with four vertices each take 1.3, 3.8 and 7.2 ms with their
+// rebuild.  At the loads a table is sized for, up to about 0.8, no probe
+// sequence gets this long.  A table sized by a hint of lattice_create has no
+// rebuild and may fill up; one of lattice_create_hierarchy has, and a hint that
+// leaves it nearly full costs the rebuild (8,160 vertices in 8,192 slots and
+// 130,800 in 131,072: 5 and 29 ms, 9 and 305 when it fills up).
 constexpr uint64_t kRetryProbes = 2048;
 
 // The insert of level L: from the positions (halved `halvings` times after
@@ -590,6 +595,7 @@ TableJob table_job(const lattice_s* L, const lattice_s* parent, int64_t* work) {
   j.h = L->hash();
   j.keys = L->vkeys;
   j.n_dev = &L->dc->counter;
+  j.err = &L->dc->err;
   j.nbr = L->nbr;
   j.ld = L->nmax;
   *work = L->nmax * kTaps;
@@ -597,6 +603,7 @@ TableJob table_job(const lattice_s* L, const lattice_s* parent, int64_t* work) {
     j.hf = parent->hash();
     j.fkeys = parent->vkeys;
     j.nf_dev = &parent->dc->counter;
+    j.err_f = &parent->dc->err;
     j.down = L->down;
     j.up = L->up;
     j.ldf = parent->nmax;
@@ -621,11 +628,11 @@ void issue_tables(lattice_s* L, const lattice_s* parent, hipEvent_t built, hipSt
   const int32_t* n_dev = &L->dc->counter;
   issue_lists(L, s);
   if (parent)
-    launch_coarse_tables(L->hash(), parent->hash(), L->vkeys, parent->vkeys, n_dev, &parent->dc->counter, L->nmax,
-                         parent->nmax, L->nbr, L->down, L->up, L->up_rows, L->nbr_rows, L->down_rows, built, s,
-                         defer);
+    launch_coarse_tables(L->hash(), parent->hash(), L->vkeys, parent->vkeys, n_dev, &parent->dc->counter,
+                         &L->dc->err, &parent->dc->err, L->nmax, parent->nmax, L->nbr, L->down, L->up, L->up_rows,
+                         L->nbr_rows, L->down_rows, built, s, defer);
   else
-    launch_neighbor_table(L->hash(), L->vkeys, n_dev, L->nmax, L->nbr, L->nmax, L->nbr_rows, s, defer);
+    launch_neighbor_table(L->hash(), L->vkeys, n_dev, &L->dc->err, L->nmax, L->nbr, L->nmax, L->nbr_rows, s, defer);
 }
 
 int enqueue_build(lattice_s* L, const float* pos, const float* y_src, float y_scale, const float a[3],

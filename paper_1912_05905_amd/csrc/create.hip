@@ -494,7 +494,10 @@ __device__ inline int32_t up_entry(const HashView& coarse, uint64_t key, int t) 
 // tap-major (table[t * ld + v]): the same-level table (9 entries per vertex),
 // and for a coarse level its Downsample table (9 per coarse vertex) and the
 // Upsample table from it into the finer level (9 per fine vertex).  Vertex
-// counts come from device memory.
+// counts come from device memory.  A level whose build raised an error bit gets
+// no tables: it is rebuilt or unusable, nothing reads them, and in a table that
+// overflowed, which is nearly full, the search for an absent key walks all slots
+// (three levels of 70,000 points with 280k vertices in 262,144 slots: 11 s).
 struct TableJobs {
   TableJob job[kMaxLevels];
 };
@@ -502,6 +505,7 @@ struct TableJobs {
 __global__ void __launch_bounds__(kBlock)
 k_level_tables(TableJobs jobs) {
   const TableJob& J = jobs.job[blockIdx.y];
+  if (*J.err != 0 || (J.err_f && *J.err_f != 0)) return;
   const int64_t nc = *J.n_dev;
   const int64_t nf = J.up ? *J.nf_dev : 0;
   const int64_t per_c = nc * kTaps;
@@ -691,13 +695,14 @@ inline unsigned stride_grid(int64_t work) {
   return static_cast<unsigned>(b < 1 ? 1 : (b < 4096 ? b : 4096));
 }
 
-void launch_neighbor_table(HashView h, const uint64_t* vkeys, const int32_t* n_dev, int64_t n_max,
-                           int32_t* nbr, int64_t ldn, int32_t* nbr_rows, hipStream_t s, RowOrderBatch* defer) {
+void launch_neighbor_table(HashView h, const uint64_t* vkeys, const int32_t* n_dev, const uint32_t* err,
+                           int64_t n_max, int32_t* nbr, int64_t ldn, int32_t* nbr_rows, hipStream_t s, RowOrderBatch* defer) {
   if (n_max <= 0) return;
   TableJob j{};
   j.h = h;
   j.keys = vkeys;
   j.n_dev = n_dev;
+  j.err = err;
   j.nbr = nbr;
   j.ld = ldn;
   launch_level_tables(&j, 1, n_max * kTaps, s);
@@ -708,14 +713,15 @@ void launch_neighbor_table(HashView h, const uint64_t* vkeys, const int32_t* n_d
 }
 
 void launch_coarse_tables(HashView coarse, HashView fine, const uint64_t* coarse_keys, const uint64_t* fine_keys,
-                          const int32_t* nc_dev, const int32_t* nf_dev, int64_t nc_max, int64_t nf_max, int32_t* nbr,
+                          const int32_t* nc_dev, const int32_t* nf_dev, const uint32_t* err,
+                          const uint32_t* err_f, int64_t nc_max, int64_t nf_max, int32_t* nbr,
                           int32_t* down, int32_t* up, int32_t* up_rows, int32_t* nbr_rows, int32_t* down_rows,
                           hipEvent_t done, hipStream_t s, RowOrderBatch* defer) {
   if (nc_max <= 0 || nf_max <= 0) {
     if (done) (void)hipEventRecord(done, s);
     return;
   }
-  TableJob j{coarse, fine, coarse_keys, fine_keys, nc_dev, nf_dev, nbr, down, up, nc_max, nf_max};
+  TableJob j{coarse, fine, coarse_keys, fine_keys, nc_dev, nf_dev, err, err_f, nbr, down, up, nc_max, nf_max};
   launch_level_tables(&j, 1, (2 * nc_max + nf_max) * kTaps, s);
   // the rows of all three tables grouped by tap mask, in one launch (or in
   // the caller's batch)

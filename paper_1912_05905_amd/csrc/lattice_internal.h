@@ -188,6 +188,8 @@ struct TableJob {
   const uint64_t* fkeys; // the finer level's (coarse levels)
   const int32_t* n_dev;  // the level's vertex count (device)
   const int32_t* nf_dev; // the finer level's (coarse levels)
+  const uint32_t* err;   // error bits of the level's build (device)
+  const uint32_t* err_f; // the finer level's (coarse levels)
   int32_t* nbr;          // same-level table, tap-major, row stride ld
   int32_t* down;         // Downsample table, row stride ld (null for the finest level)
   int32_t* up;           // Upsample table, row stride ldf (null for the finest level)
@@ -230,11 +232,12 @@ void launch_fill_lists(HashView h, const int32_t* slot, const int32_t* rank, con
 // the table, then its rows grouped by tap mask within ranges of 4096
 // (nbr_rows); with `defer` the row order is added to that batch instead of
 // launched
-void launch_neighbor_table(HashView h, const uint64_t* vkeys, const int32_t* n_dev, int64_t n_max,
-                           int32_t* nbr, int64_t ldn, int32_t* nbr_rows, hipStream_t s,
+void launch_neighbor_table(HashView h, const uint64_t* vkeys, const int32_t* n_dev, const uint32_t* err,
+                           int64_t n_max, int32_t* nbr, int64_t ldn, int32_t* nbr_rows, hipStream_t s,
                            RowOrderBatch* defer = nullptr);
 void launch_coarse_tables(HashView coarse, HashView fine, const uint64_t* coarse_keys, const uint64_t* fine_keys,
-                          const int32_t* nc_dev, const int32_t* nf_dev, int64_t nc_max, int64_t nf_max, int32_t* nbr,
+                          const int32_t* nc_dev, const int32_t* nf_dev, const uint32_t* err,
+                          const uint32_t* err_f, int64_t nc_max, int64_t nf_max, int32_t* nbr,
                           int32_t* down, int32_t* up, int32_t* up_rows, int32_t* nbr_rows, int32_t* down_rows,
                           hipEvent_t done, hipStream_t s, RowOrderBatch* defer = nullptr);
 // the batch's row orders in one launch (`done`, if given, bound to it)

@@ -3,6 +3,8 @@ remainders, the smallest and largest of a dispatch range), against the
 oracle.  The tolerances are those of the parity tests."""
 from __future__ import annotations
 
+import time
+
 import numpy as np
 import pytest
 
@@ -263,7 +265,22 @@ def test_first_table_sizes(L, O, m, sigma, hierarchy):  # noqa: F811
         g.destroy()
 
 
-# a hinted table is not rebuilt: it may fill up, however long the probe sequences get
+# a table that overflows is rebuilt at once: no convolution tables are looked up in a full one, where every absent key walks
+# all slots (three levels of this cloud took 11 s in all that way, and take 8 ms)
+def test_overflow_takes_no_lookups_in_a_full_table(L):
+    pos = _dev(_cloud(2602, 70_000, 1.0))
+    L.Lattice.create_hierarchy(pos, [0.5] * 3, 3)[2].n
+    torch.cuda.synchronize()
+    start = time.perf_counter()
+    gls = L.Lattice.create_hierarchy(pos, [0.001] * 3, 3)
+    assert [g.n > 262_144 for g in gls] == [True] * 3
+    torch.cuda.synchronize()
+    assert time.perf_counter() - start < 2.0
+    for g in reversed(gls):
+        g.destroy()
+
+
+# a table hinted to lattice_create is not rebuilt: it may fill up, however long the probe sequences get
 def test_hinted_table_nearly_full(L, O):  # noqa: F811
     pos = _cloud(2601, 2040, 1.0)
     ol = O.Lattice.create(pos, np.full(3, 0.002, np.float32))
