@@ -656,29 +656,29 @@ int ensure_lists(lattice_s* L, hipStream_t s) {
   return check_launch("lattice lists");
 }
 
-// Table size for a build: the caller's hint, else 2 slots per point for
-// the first level (dense surface clouds have at most about one vertex per
-// point) and 2 per parent vertex for coarse levels.  Small clouds are sparse
-// on the lattice's scale (2,047-point objects, rooms and scans have 2 to 4
-// vertices per point) and their tables cost little to clear: up to 16,384
-// points the first level's table takes the worst case (2 slots per reference,
-// no overflow), up to 65,536 half of it.  Create + splat with 2 slots per point
-// and with this rule: object of 2,047 points at a load of 0.74 119 and 72 us,
-// and where the table overflowed and was rebuilt at every build, 7.8 and
-// 0.08 ms; rooms of 2,047, 16,384 and 65,536 points 8.4, 85 and 429 ms against
-// 0.09, 0.10 and 0.15; dense clouds (objects and scans of 10,000 to 65,536
-// points) 74 to 97 us either way.  A table that overflows is rebuilt at the
-// worst-case size (2 slots per vertex reference) from the handle's own
-// elevated positions, so no caller buffer is needed again.
+// Table size for a build: the caller's hint, else 2 slots per parent vertex for
+// a coarse level whose parent's count is read back, else 2 slots per point
+// (surface clouds have at most about one vertex per point, and a coarse level
+// about as many vertices as its parent at most).  Small clouds are sparse on the
+// lattice's scale (2,047-point objects, rooms and scans have 2 to 4 vertices per
+// point) and their tables cost little to clear: up to 16,384 points a table takes
+// the worst case (2 slots per reference, no overflow), up to 65,536 half of it.
+// Create + splat with 2 slots per point and with this rule: object of 2,047
+// points at a load of 0.74 119 and 72 us, and where the table overflowed and was
+// rebuilt at every build, 7.8 and 0.08 ms; rooms of 2,047, 16,384 and 65,536
+// points 8.4, 85 and 429 ms against 0.09, 0.10 and 0.15; dense clouds (objects
+// and scans of 10,000 to 65,536 points) 74 to 97 us either way.  Three levels of
+// 3,000 and 10,000 points with four vertices each: 3.8 and 3.7 ms with 2 slots on
+// the coarse levels, 0.07 and 0.09 here; of an object of 500 points 0.86 and
+// 0.06.  A table that overflows is rebuilt at the worst-case size (2 slots per
+// vertex reference) from the handle's own elevated positions, so no caller buffer
+// is needed again.
 int64_t initial_capacity(const lattice_s* L, const lattice_s* parent, int64_t capacity_hint) {
   const int64_t refs = 4 * L->m;
   const int64_t full = next_pow2(std::max<int64_t>(1024, 2 * refs));
   if (capacity_hint > 0) return next_pow2(std::max<int64_t>(1024, 2 * std::min(capacity_hint, refs)));
   if (parent && parent->counts_known) return std::min(full, next_pow2(std::max<int64_t>(1024, 2 * parent->n)));
-  // a finest level, or a coarse one whose parent's count is not read back
-  // yet: 2 slots per point (a coarse level has at most about as many
-  // vertices as its parent)
-  const int64_t slots = parent || L->m > 65536 ? 2 : (L->m > 16384 ? 4 : 8);
+  const int64_t slots = L->m > 65536 ? 2 : (L->m > 16384 ? 4 : 8);
   return std::min(full, next_pow2(std::max<int64_t>(1024, slots * L->m)));
 }
 

@@ -265,6 +265,24 @@ def test_first_table_sizes(L, O, m, sigma, hierarchy):  # noqa: F811
         g.destroy()
 
 
+# up to 16,384 points no level of a hierarchy overflows, however sparse the cloud: the tables are built once, as for a dense one
+@pytest.mark.parametrize("m", [1, 500, 3000, 16_384])
+def test_small_hierarchies_are_built_once(L, m):  # noqa: F811
+    pos = _dev(_cloud(2603, m, 1.0))
+    launches = []
+    L.timing_enable("nbr")
+    for sigma in (0.5, 0.001):
+        L.timing_read("nbr")   # (reading clears)
+        gls = L.Lattice.create_hierarchy(pos, [sigma] * 3, 3)
+        assert sigma > 0.1 or [g.n for g in gls][0] > 3.9 * m
+        torch.cuda.synchronize()
+        launches.append(L.timing_read("nbr")[0])
+        for g in reversed(gls):
+            g.destroy()
+    L.timing_enable("nbr", False)
+    assert launches[0] == launches[1] > 0
+
+
 # a table that overflows is rebuilt at once: no convolution tables are looked up in a full one, where every absent key walks
 # all slots (three levels of this cloud took 11 s in all that way, and take 8 ms)
 def test_overflow_takes_no_lookups_in_a_full_table(L):
