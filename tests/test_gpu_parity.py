@@ -180,20 +180,21 @@ def test_device_errors(L):
 
 def test_overflow_rebuild_of_a_hierarchy(L, O):
     """Points far apart on the lattice's scale: nearly 4 vertices per point
-    overflow the table sized from the point count.  The coarse levels are
-    enqueued before the fine level's count is read back, so each is built
-    from a table that overflowed; the first read rebuilds the fine level,
-    then each coarse level from the rebuilt one.  Structure and the
-    strided / transposed convolutions must match the oracle."""
-    pos = _cloud(71, 3000, 1.0)
-    sigma = 0.002
+    overflow the table of 2 slots per point that clouds beyond 65,536 points
+    get.  The coarse levels are enqueued before the fine level's count is
+    read back, so each is built from a table that overflowed; the first read
+    rebuilds the fine level, then each coarse level from the rebuilt one.
+    Structure and the strided / transposed convolutions must match the
+    oracle."""
+    pos = _cloud(71, 70_000, 1.0)
+    sigma = 0.001
     g0 = L.Lattice.create(_dev(pos), [sigma] * 3)
     g1 = g0.coarsen()
     g2 = g1.coarsen()
     o0 = O.Lattice.create(pos, np.full(3, sigma, np.float32))
     o1 = o0.coarsen()
     o2 = o1.coarsen()
-    assert o0.n > 2 * 3000 * 1.3          # beyond the first table's reach
+    assert o0.n > 262_144                 # more vertices than the first table has slots
     g2o = [_check_structure(g, o) for g, o in ((g2, o2), (g1, o1), (g0, o0))][::-1]
     rng = np.random.default_rng(12)
     for (gf, of, pf), (gc, oc, pc) in (((g0, o0, g2o[0]), (g1, o1, g2o[1])), ((g1, o1, g2o[1]), (g2, o2, g2o[2]))):
@@ -288,13 +289,13 @@ def test_create_hierarchy_overflow_rebuild(L, O):
     scale: every level's first table overflows (nearly 4 vertices per
     point), the first read rebuilds the fine level and then each coarse
     level from the rebuilt one, as for create + coarsen."""
-    pos = _cloud(72, 3000, 1.0)
-    sigma = 0.002
+    pos = _cloud(72, 70_000, 1.0)
+    sigma = 0.001
     gls = L.Lattice.create_hierarchy(_dev(pos), [sigma] * 3, 3)
     ols = [O.Lattice.create(pos, np.full(3, sigma, np.float32))]
     for _ in range(2):
         ols.append(ols[-1].coarsen())
-    assert ols[0].n > 2 * 3000 * 1.3
+    assert min(o.n for o in ols) > 262_144
     g2o = [_check_structure(g, o) for g, o in zip(gls[::-1], ols[::-1])][::-1]
     _check_down_up(np.random.default_rng(13), g2o, gls, ols)
 
@@ -304,9 +305,9 @@ def test_rebuild_ordered_for_another_stream(L, O):
     by the first call that needs its vertex count; an operator called on
     another stream (here with other work still queued on the first) is
     ordered after that rebuild, without host synchronisation."""
-    pos = _cloud(73, 3000, 1.0)
-    sigma = 0.002
-    F = np.random.default_rng(74).normal(size=(3000, 8)).astype(np.float32)
+    pos = _cloud(73, 70_000, 1.0)
+    sigma = 0.001
+    F = np.random.default_rng(74).normal(size=(70_000, 8)).astype(np.float32)
     pd, Fd = _dev(pos), _dev(F)
     big = torch.randn((2048, 2048), device="cuda")
     torch.cuda.synchronize()
@@ -319,7 +320,7 @@ def test_rebuild_ordered_for_another_stream(L, O):
         got = gl.splat(Fd)
     torch.cuda.synchronize()
     ol = O.Lattice.create(pos, np.full(3, sigma, np.float32))
-    assert ol.n > 2 * 3000 * 1.3              # beyond the first table's reach
+    assert ol.n > 262_144                     # more vertices than the first table has slots
     g2o = _check_structure(gl, ol)
     P.assert_close(P.rows_in_oracle_order(_host(got), g2o), ol.splat(F)[0], P.TOL_F32, "splat")
     gl.destroy()
@@ -473,23 +474,34 @@ def test_conv_fp32(L, O, cin, cout):
         P.assert_close(P.rows_in_oracle_order(_host(gy), g2o), oy, P.TOL_F32, f"conv {cin}->{cout}")
 
 
-def test_conv_input_beyond_buffer_reach(L, O):
+@pytest.mark.parametrize("dtype,pre", [("f32", False), ("f32", True), ("bf16", False), ("bf16", True)])
+def test_conv_input_beyond_buffer_reach(L, O, dtype, pre):
     """An input whose rows span more than 2 GiB (a wide row stride) takes the
-    convolution path without buffer resources."""
+    convolution path without buffer resources, plain and pre-activated."""
     pos = _cloud(77, 3000, 0.8)
     gl, ol, g2o = _pair(L, O, pos, 0.07)
-    cin = cout = 64
-    ld = ((2**31 // (4 * max(ol.n - 1, 1)) + 64) // 8) * 8
-    assert (ol.n - 1) * ld * 4 > 2**31
+    cin, cout = 72, 64
+    bf = dtype == "bf16"
+    size, td = (2, torch.bfloat16) if bf else (4, torch.float32)
+    rnd = O.round_bf16 if bf else (lambda a: a.astype(np.float32))
+    ld = ((2**31 // (size * max(ol.n - 1, 1)) + 64) // 8) * 8
+    assert (ol.n - 1) * ld * size > 2**31
     rng = np.random.default_rng(77)
-    X = rng.normal(size=(ol.n, cin)).astype(np.float32)
-    W = _rand_w(rng, cin, cout, 1.0 / np.sqrt(9 * cin))
-    big = torch.empty((ol.n, ld), dtype=torch.float32, device="cuda")
-    big[:, :cin] = _dev(X[g2o])
-    gy = gl.conv(gl, big[:, :cin], _gpu_w(W), relu=True)
+    X = rnd(rng.normal(size=(ol.n, cin)))
+    W = rnd(_rand_w(rng, cin, cout, 1.0 / np.sqrt(9 * cin)))
+    big = torch.empty((ol.n, ld), dtype=td, device="cuda")
+    big[:, :cin] = _dev(np.asarray(X, np.float32)[g2o], td)
+    gW = _gpu_w(np.asarray(W, np.float32), td)
+    A = X.astype(np.float64)
+    if pre:
+        gy = gl.conv_preact(gl, big[:, :cin], gW, groups=4, relu=True)
+        A = rnd(O.groupnorm(A, 4, eps=1e-5, relu=True)).astype(np.float64)
+    else:
+        gy = gl.conv(gl, big[:, :cin], gW, relu=True)
     del big
-    oy = ol.conv(ol, X.astype(np.float64), W.astype(np.float64), relu=True)
-    P.assert_close(P.rows_in_oracle_order(_host(gy), g2o), oy, P.TOL_F32, "conv, 2 GiB input")
+    oy = rnd(ol.conv(ol, A, W.astype(np.float64), relu=True))
+    P.assert_close(P.rows_in_oracle_order(_host(gy), g2o), oy, P.TOL_BF16 if bf else P.TOL_F32,
+                   f"conv, 2 GiB input {dtype} pre={pre}")
 
 
 @pytest.mark.parametrize("cin,cout", [(64, 64), (8, 24), (128, 192), (384, 192), (256, 256)])
