@@ -121,11 +121,14 @@ def test_distribute_backward_maximum_beside_nan(L, O):  # noqa: F811
     assert seen > 100
 
 
-# convolution: rows and columns that do not fill a tile, channels that do not fill a stage, odd and even stage counts,
-# every tile of the dispatch that a small lattice reaches
+# convolution: rows and columns that do not fill a tile, channels that do not fill a stage, odd and even stage counts (in
+# bf16 also 1 to 3 stages behind the groups of four of the 128 x 128 tiles), every tile of the dispatch that a small lattice
+# reaches
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("m,cin,cout,pre", [(1, 8, 24, False), (40, 40, 40, True), (300, 72, 136, False),
-                                            (900, 136, 72, True), (5000, 64, 128, True), (9000, 32, 320, False)])
+                                            (900, 136, 72, True), (5000, 64, 128, True), (9000, 32, 320, False),
+                                            (300, 264, 128, False), (301, 264, 128, True), (302, 296, 128, False),
+                                            (303, 296, 128, True), (304, 328, 128, False), (305, 328, 128, True)])
 def test_conv_tiles(L, O, m, cin, cout, pre, dtype):  # noqa: F811
     gl, ol, g2o = _pair(L, O, _cloud(2300 + m, m, 0.7), 0.05)
     gc, oc = gl.coarsen(), ol.coarsen()
