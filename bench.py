@@ -89,10 +89,28 @@ def default_pipelines(wl) -> int:
     return default_layout(wl)[0]
 
 
+SOLO_WARMUP, SOLO_STEPS = 5, 100   # warmup and at most this many steps on a pipeline of its own
+
+
+def run_counts(steps, warmup, pipelines):
+    """(steps, hierarchies built) of a whole run of this benchmark: warmup,
+    the instrumented step, two timed regions and, with several pipelines,
+    the steps on one pipeline of its own.  Every pipeline builds its next
+    cloud's lattices one step ahead, so one hierarchy more than it steps."""
+    n = warmup + 1 + 2 * steps
+    builds = n + pipelines
+    if pipelines > 1:
+        solo = SOLO_WARMUP + min(steps, SOLO_STEPS)
+        n += solo
+        builds += solo + 1
+    return n, builds
+
+
 def summarize_pmc(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, copy_mb, steps, warmup, key, pipelines=2):
     """Per-family HBM bytes per step from rocprofv3 --pmc FETCH_SIZE and
-    WRITE_SIZE runs of this benchmark, each counter scaled by what it reads
-    for a device-to-device copy of copy_mb MiB.  Appends the result to
+    WRITE_SIZE runs of this benchmark with these steps, warmup and pipelines,
+    each counter scaled by what it reads for a device-to-device copy of
+    copy_mb MiB.  Appends the result to
     profiles/traffic.json under `key`."""
     import csv
     import glob
@@ -131,11 +149,9 @@ def summarize_pmc(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, copy_mb,
             ent[field] += sum(vals) * scale
             if counter == "FETCH_SIZE":
                 ent["dispatches"] += len(vals)
-    runs = warmup + 1 + 2 * steps  # warmup, instrumented step, the two timed regions of the profiled run
+    runs, builds = run_counts(steps, warmup, pipelines)
     for fam, ent in fams.items():
-        # each pipeline builds its next cloud's lattices one step ahead: one
-        # more hierarchy per pipeline than steps
-        n = runs + pipelines if fam in BUILD_FAMILIES else runs
+        n = builds if fam in BUILD_FAMILIES else runs
         ent["fetch_bytes_per_step"] = ent.pop("fetch_bytes") / n
         ent["write_bytes_per_step"] = ent.pop("write_bytes") / n
         ent["dispatches_per_step"] = ent.pop("dispatches") / n
@@ -520,8 +536,8 @@ def main():
     one_ms = None
     if args.streams > 1:
         solo = GpuPipeline(wl, overlap=True)
-        n_solo = min(args.steps, 100)
-        for _ in range(5):
+        n_solo = min(args.steps, SOLO_STEPS)
+        for _ in range(SOLO_WARMUP):
             levels_s, _, _ = solo.step()
             solo.finish_step(levels_s)
         torch.cuda.synchronize()
