@@ -635,20 +635,26 @@ int64_t blocks_of(int64_t n_out, int Cout, int rows, int cols) {
   return ((n_out + rows - 1) / rows) * ((Cout + cols - 1) / cols);
 }
 
-// Tile choice, from sweeps over the lattices of a LiDAR scan and of rooms on
+// Tile choice, from sweeps over the lattices of LiDAR scans and of rooms on
 // MI355X (us per convolution; tile rows x columns / bytes of channels a stage).
 // fp32: at 900 tiles of 32 x 64 and more, stages of 32 channels (128->128 on 16k
 // vertices: 48 against 53 for 64-channel stages and for 32 x 32; 128->64 Upsample
-// into 212k: 60 against 75 and 63); from 500 tiles 64-channel stages (256->256 on
-// 6.4k vertices: 67 against 73 and 79); below that, 32 x 32 tiles, as more
-// workgroups matter more than the operand bytes per product (128->128 on 6.4k: 26
-// against 28; 256->256 on 2.2k: 44 against 49).  64 x 64 tiles were slower
-// everywhere (down to one workgroup per compute unit, nothing hides a wave's own
-// waits).  bf16: 128 x 128 tiles halve the gathered bytes per product and win
-// once there are enough of them (wide layers, large levels), with four stages
-// in flight (256->256 on 239k vertices: 1137 against 1226 us for the ResNet block);
-// 128 x 64 for 64 output channels on large levels (half the weight rows per
-// output row); 64 x 64 otherwise.
+// into 212k: 60 against 75 and 63); from 500 tiles 64-channel stages: at 500 to
+// 800 tiles pre-activated convolutions are 1 to 6% faster with them and plain ones
+// 2 to 7% slower (256->256 on 6.4k vertices, 800 tiles: pre-activated 95 and 101,
+// plain 79 and 78); below that, 32 x 32 tiles, as more workgroups matter more than
+// the operand bytes per product (128->128 on 6.4k, 400 tiles: 26 against 27, on
+// 4.4k, 274 tiles: 20 against 23; 256->256 on 2.3k: 37 against 46).  64 x 64 tiles
+// were slower everywhere (down to one workgroup per compute unit, nothing hides a
+// wave's own waits).  bf16: 128 x 128 tiles halve the gathered bytes per product
+// and win once there are enough of them, with four stages in flight: from 400
+// tiles for wide inputs (256->128 on 52k vertices, 410 tiles: 55 against 59 for 64
+// x 64; 256->256 there 96 against 102, on 23k, 356 tiles, 49 against 47, on 2.3k,
+// 36 tiles, 34 against 15; the ResNet block of 256 channels on 239k 1137 against
+// 1226), from 1,500 for others; 128 x 64 for 64 output channels on large levels
+// (half the weight rows per output row); 64 x 64 otherwise, with two stages in
+// flight at any size (64->96 on 819k vertices: 325 with three stages of the former
+// pipeline, 225 here).
 // PRE (the pre-activated convolution) uses the same tiles, apart from the
 // register kernel for narrow outputs, which has no pre-activation.
 template <bool BF16, bool PRE>
@@ -672,7 +678,7 @@ void conv_dispatch(const int32_t* nbr, int64_t ldn, int64_t n_out, const void* i
   if constexpr (BF16) {
     const int64_t b128 = blocks_of(n_out, Cout, 128, 128);
     const int64_t b64 = blocks_of(n_out, Cout, 64, 64);
-    if (Cout >= 128 && (b128 >= 1500 || (Cin >= 256 && Cout % 128 == 0))) CONV_GO(128, 128, 2, 2, 64, 4);
+    if (Cout >= 128 && (b128 >= 1500 || (Cin >= 256 && Cout % 128 == 0 && b128 >= 400))) CONV_GO(128, 128, 2, 2, 64, 4);
     if (Cout == 64 && b64 >= 8192) CONV_GO(128, 64, 2, 2, 64, 2);
     if (Cout > 32 && b64 >= 256) CONV_GO(64, 64, 2, 2, 128, 2);
     CONV_GO(32, 32, 2, 2, 128, 2);
