@@ -812,8 +812,13 @@ __device__ inline void stage_classifier(float* wl, const float* __restrict__ Wc,
 
 // Sums over the channels in short chains (a single chain through the products
 // doubles the rounding error): four chains, one per channel of a lane's four,
-// over kClassifyRun blocks of 16 channels, then added to the total.
+// over kClassifyRun blocks of 16 channels make a run; where there are more than
+// two runs, two are added before they go to the total.  (Relative error against
+// 64 bits at 128 and 256 fp32 channels 1.07e-7 and 1.09e-7, with runs added to the
+// total one by one 1.08e-7 and 1.12e-7, by lane groups 1.05e-7 and 1.06e-7.  The
+// wide rows below add them one by one: pairs cost 10 to 50% there.)
 constexpr int kClassifyRun = 2;
+constexpr int kOffsetRun = 4;
 template <int NB>
 struct ClassSums {
   f32x4_v run[4][NB], total[NB];
@@ -832,10 +837,23 @@ struct ClassSums {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) run[e][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[nb][e], f, run[e][nb], 0, 0, 0);
   }
-  __device__ inline void flush() {
+  // the run's sum, and on to the next run
+  __device__ inline void take(f32x4_v (&t)[NB]) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) total[nb] += (run[0][nb] + run[1][nb]) + (run[2][nb] + run[3][nb]);
+    for (int nb = 0; nb < NB; ++nb) t[nb] = (run[0][nb] + run[1][nb]) + (run[2][nb] + run[3][nb]);
     clear();
+  }
+  __device__ inline void flush() {
+    f32x4_v t[NB];
+    take(t);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) total[nb] += t[nb];
+  }
+  __device__ inline void flush(const f32x4_v (&before)[NB]) {
+    f32x4_v t[NB];
+    take(t);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) total[nb] += before[nb] + t[nb];
   }
 };
 
@@ -1012,8 +1030,7 @@ k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, in
       ClassSums<NB> sums;
       const float* f = T + (mg * 16 + li) * PITCH + 4 * lg;
       const f32x4_v* wf = reinterpret_cast<const f32x4_v*>(wl) + lane;
-#pragma unroll 1
-      for (int c0 = 0; c0 < BLK; c0 += kClassifyRun) {
+      auto add_run = [&](int c0) {
 #pragma unroll
         for (int cb = c0; cb < c0 + kClassifyRun; ++cb) {
           if (BLK % kClassifyRun != 0 && cb >= BLK) break;
@@ -1025,7 +1042,23 @@ k_deform_classify(const int4* __restrict__ idx, const float4* __restrict__ w, in
 #pragma unroll
           for (int e = 0; e < 4; ++e) sums.add(wr, e, x[e]);
         }
-        sums.flush();
+      };
+      if constexpr (BLK > 2 * kClassifyRun) {
+        static_assert(BLK % (2 * kClassifyRun) == 0, "pairs of runs");
+#pragma unroll 1
+        for (int c0 = 0; c0 < BLK; c0 += 2 * kClassifyRun) {
+          f32x4_v first[NB];
+          add_run(c0);
+          sums.take(first);
+          add_run(c0 + kClassifyRun);
+          sums.flush(first);
+        }
+      } else {
+#pragma unroll 1
+        for (int c0 = 0; c0 < BLK; c0 += kClassifyRun) {
+          add_run(c0);
+          sums.flush();
+        }
       }
       f32x4_v acc[NB];
 #pragma unroll
@@ -1094,8 +1127,16 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
         if (TAIL && c >= C) x[k] = f32x4_v{0.f, 0.f, 0.f, 0.f};
       }
     };
+    // the offsets' sums in short chains too: kOffsetRun blocks, then the total
     const int full = C / 16;
-    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    float part[4] = {0.f, 0.f, 0.f, 0.f}, run[4] = {0.f, 0.f, 0.f, 0.f};
+    auto flush = [&]() {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        part[k] += run[k];
+        run[k] = 0.f;
+      }
+    };
     auto offsets = [&](int cb, auto tail_c) {
       f32x4_v x[4];
       gather(cb, x, tail_c);
@@ -1110,11 +1151,15 @@ k_deform_classify_wide(const int4* __restrict__ idx, const float4* __restrict__ 
           mx = fmaxf(mx, qk[k]);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) part[k] += (qk[k] - mx) * wv[e];
+        for (int k = 0; k < 4; ++k) run[k] += (qk[k] - mx) * wv[e];
       }
     };
-    for (int cb = 0; cb < full; ++cb) offsets(cb, std::false_type{});
+    for (int cb = 0; cb < full; ++cb) {
+      offsets(cb, std::false_type{});
+      if (cb % kOffsetRun == kOffsetRun - 1) flush();
+    }
     if (full < blocks) offsets(full, std::true_type{});
+    flush();
     float coef[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -1438,6 +1483,9 @@ inline int lanes_per_row(int C, bool bf16) {
 // per-entry bookkeeping per channel), every other width one chunk per lane.
 // DeformSlice and its gradient must agree: the gradient recomputes the
 // offsets, and the same lane groups sum the dot products in the same order.
+// (The classifier sums them in this order too, except on the matrix cores for
+// rows over kClassifyTileC channels, where its offsets may differ from the
+// gradient's by the rounding of the order; the argmax is taken before the sum.)
 inline int point_lanes_per_row(int C, bool bf16) {
   return !bf16 && C / 4 == 16 ? 8 : lanes_per_row(C, bf16);
 }

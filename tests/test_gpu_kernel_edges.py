@@ -205,6 +205,28 @@ def test_classifier_tiles(L, O, m, C, K, dtype):  # noqa: F811
     P.assert_close(_host(got), ref, P.TOL_F32, f"logits m={m} C={C} K={K} {dtype}")
 
 
+# sums of many channels run in short chains: the error of the logits against float64 over that of DeformSlice's own rows
+# classified in float64.  Measured 1.22, 1.50, 1.32 and 1.53; by lane groups, which sum in trees, 1.20, 1.46, 1.22 and 1.32;
+# with the offsets of wide rows in one chain and runs added one by one 1.22, 1.55, 1.59 and 2.05.  The inputs are fixed, and
+# the order of a sum moves a ratio by less than 0.02.
+@pytest.mark.parametrize("C,bound", [(128, 1.25), (256, 1.53), (264, 1.4), (512, 1.65)])
+def test_classifier_rounding_error(L, C, bound):  # noqa: F811
+    gl = L.Lattice.create(_dev(_cloud(2460, 60_000, 1.0)), [0.05] * 3)
+    idx, w = gl.simplices()
+    gen = torch.Generator("cuda").manual_seed(C)
+    x = torch.randn((gl.n, C), generator=gen, device="cuda")
+    wv = torch.randn(C, generator=gen, device="cuda") / np.sqrt(C)
+    Wc = torch.randn((20, C), generator=gen, device="cuda") / np.sqrt(C)
+    got = gl.deform_slice_classify(x, wv, 0.1, Wc).double()
+    own = gl.deform_slice(x, wv, 0.1)
+    own = (own[0] if isinstance(own, tuple) else own).double() @ Wc.double().T
+    rows, b = x.double()[idx.long()], w.double()[..., None]
+    q = b * rows
+    db = torch.tanh(0.1 + (q - q.max(1, keepdim=True).values) @ wv.double())
+    ref = ((b + db[..., None]) * rows).sum(1) @ Wc.double().T
+    assert float((got - ref).norm() / (own - ref).norm()) < bound
+
+
 # infinite values in the last channels of a row that does not fill its lanes: the logits are infinite or NaN where the
 # formula makes them so and nowhere else (tiled form, wide rows, lane groups)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
