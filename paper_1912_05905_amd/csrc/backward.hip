@@ -33,7 +33,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // (wsum) or is summed over J_v by the lanes (0 where the sum is 0, as in the
 // forward).  The slice that follows folds these factors into its weights:
 // dividing the rows of dL/dx first wrote and read them once more (35 against
-// 12 us in front of the slice, for 128 channels of a 200k-point room).
+// 12 us in front of the slice, for 128 channels of a 200k-point room).  Narrow
+// rows of large clouds gain nothing (16 channels of 1M points 90 against 83 us,
+// of 200k 22 against 24).
 constexpr int kScaleLanes = 16;
 
 __global__ void __launch_bounds__(kBlock)
@@ -365,6 +367,9 @@ inline unsigned blocks_for(int64_t threads) { return static_cast<unsigned>((thre
 // more than small chunks gain, and more than 8 chunks have at least 256
 // vertices: 128 x 128 fp32 on 1.3k and 3.1k vertices 18.5 and 24.5 us with 64,
 // 12.7 and 20.8 here; with 8 chunks 256 x 256 on 1.3k takes 29.7, with 6 31.5.
+// Wide layers have 8 chunks where 512 workgroups in all would be one (512 x 512:
+// 75 MB of partials instead of 9.4): 76 and 391 us on 1.3k and 8.4k vertices, with
+// one chunk and operands through LDS 101 and 653.
 void wgrad_chunks(int64_t n_out, int tiles, int64_t* chunks, int64_t* V) {
   int64_t want = std::max<int64_t>(8, (kWgTargetBlocks / (9 * static_cast<int64_t>(tiles)) + 7) / 8 * 8);
   if (tiles >= 3) want = std::min<int64_t>(want, std::max<int64_t>(8, (n_out + 255) / 256));
